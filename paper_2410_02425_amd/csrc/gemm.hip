@@ -17,7 +17,8 @@
 //    two 128-row workgroups per CU for launches of at least 512 tiles.
 //  * gemm_big: 16-bit MFMA for the remaining prefill shapes, 128x128x64 tiles
 //    staged in LDS.
-//  * gemm_f32: fp32 FMA tiles for the fp32 model path (any M).
+//  * gemm_f32_mfma: fp32 matrix instructions for the fp32 model path (any M);
+//    gemm_f32, FMA tiles with element loads, where rows are not on 16 bytes.
 #include <algorithm>
 
 #include <hip/hip_ext.h>
@@ -821,6 +822,90 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
   }
 }
 
+// The fp32 path on the fp32 matrix instruction (16x16x4, products and sums in
+// fp32).  A workgroup owns one tile of 16 MT rows x 16 NT columns; its KW
+// waves take every KW-th 16-wide K piece, each straight from global memory
+// (X and W are both K-contiguous, so a lane's float4 holds its row's K for
+// four MFMAs and no LDS staging is needed), and the waves' sums meet in LDS.
+// What bounds the small model's launches is the chain of memory round trips,
+// not bandwidth: a wave requests F_U pieces at once, so K = 256 costs one
+// round trip where the 64x64 LDS tile of gemm_f32_kernel costs sixteen.
+// Measured per launch over the fp32 tiny model's steps (N = 256..1,376,
+// K = 256..688, rocprofv3): 27.7 us before, 3.9 us now; 4,096 x 1,376 x 256:
+// 94.5 -> 62.3 us.
+//   * MT = NT = 1, eight waves: few rows, the most workgroups.
+//   * MT = NT = 2, four waves: half the operand reads per flop, taken above
+//     F_SMALL_TILES tiles of 16 x 16 (in graphs of back-to-back launches,
+//     K = 256: 512 tiles 4.7 against 5.7 us, 688 tiles 6.2 against 5.9, 1,376
+//     tiles 10.3 against 8.5, 5,504 tiles 31.7 against 19.8).
+constexpr int64_t F_SMALL_TILES = 640;
+constexpr int F_U = 3;  // K pieces requested together
+
+template <int MT, int NT, int KW>
+__global__ __launch_bounds__(KW * 64) void gemm_f32_mfma_kernel(const float *__restrict__ X, int64_t ldx,
+                                                                const float *__restrict__ W, int M, int N, int K,
+                                                                Epi ep) {
+  constexpr int TM = MT * 16, TN = NT * 16;
+  __shared__ float red[KW][TM][TN + 1];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r16 = lane & 15, k4 = (lane >> 4) * 4;
+  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
+  const float *xr[MT], *wr[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xr[i] = X + (int64_t)min(m0 + i * 16 + r16, M - 1) * ldx;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) wr[j] = W + (int64_t)min(n0 + j * 16 + r16, N - 1) * K;
+  floatx4_t acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  for (int kb = wave * 16; kb < K; kb += KW * 16 * F_U) {
+    floatx4_t a[F_U][MT], b[F_U][NT];
+#pragma unroll
+    for (int u = 0; u < F_U; ++u) {
+      const int k = min(kb + u * KW * 16 + k4, K - 4);  // K % 4 == 0
+#pragma unroll
+      for (int i = 0; i < MT; ++i) a[u][i] = *(const floatx4_t *)(xr[i] + k);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) b[u][j] = *(const floatx4_t *)(wr[j] + k);
+    }
+#pragma unroll
+    for (int u = 0; u < F_U; ++u) {
+      if (kb + u * KW * 16 + k4 >= K) {  // past K: both operands 0
+#pragma unroll
+        for (int i = 0; i < MT; ++i) a[u][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NT; ++j) b[u][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], b[u][j][e], acc[i][j], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][i * 16 + (lane >> 4) * 4 + r][j * 16 + r16] = acc[i][j][r];
+  __syncthreads();
+  for (int p = threadIdx.x; p < TM * TN / 2; p += KW * 64) {
+    const int row = p / (TN / 2), c = p % (TN / 2) * 2;
+    float v0 = 0.f, v1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < KW; ++w) {
+      v0 += red[w][row][c];
+      v1 += red[w][row][c + 1];
+    }
+    if (m0 + row < M && n0 + c < N) epi_pair<float>(ep, m0 + row, n0 + c, v0, v1);
+  }
+}
+
 // ------------------------------------------------------------------ dispatch
 
 // Launch shapes of the decode kernel, chosen from the weight matrix shape by
@@ -974,6 +1059,18 @@ template <>
 void launch_gemm<float>(const float *X, int64_t ldx, const float *W, int M, int N, int K, int /*splits*/,
                         float * /*part*/, const Epi &ep, hipStream_t s, const hipEvent_t *timing) {
   if (M <= 0 || N <= 0) return;
+  // The matrix-instruction kernel reads whole float4 of each row: rows on 16
+  // bytes (the documented layout); anything else takes the element loads.
+  if ((((uintptr_t)X | (uintptr_t)W) & 15) == 0 && ldx % 4 == 0 && K % 4 == 0) {
+    const int64_t tiles16 = (int64_t)((N + 15) / 16) * ((M + 15) / 16);
+    if (tiles16 <= F_SMALL_TILES)
+      launch_k(gemm_f32_mfma_kernel<1, 1, 8>, dim3((N + 15) / 16, (M + 15) / 16), 512, s, timing, X, ldx, W, M, N, K,
+               ep);
+    else
+      launch_k(gemm_f32_mfma_kernel<2, 2, 4>, dim3((N + 31) / 32, (M + 31) / 32), 256, s, timing, X, ldx, W, M, N, K,
+               ep);
+    return;
+  }
   dim3 grid((N + F_BN - 1) / F_BN, (M + F_BM - 1) / F_BM);
   launch_k(gemm_f32_kernel, grid, 256, s, timing, X, ldx, W, M, N, K, ep);
 }

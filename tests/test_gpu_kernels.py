@@ -247,6 +247,32 @@ def test_gemm_f32(M, N, K):
     assert np.all(np.abs(Y.cpu().numpy() - ref) <= bound)
 
 
+@pytest.mark.parametrize("M,N,K,shift", [
+    (1, 2, 8, 0), (16, 16, 16, 0), (17, 18, 24, 0), (4, 1376, 256, 0), (33, 100, 688, 0),   # 16 x 16 tiles
+    (640, 256, 40, 0), (641, 254, 392, 0),                                                 # at and past 640 tiles
+    (5, 66, 88, 1),                                                 # rows off 16 bytes: the element-load kernel
+])
+def test_gemm_f32_tiles(M, N, K, shift):
+    """Edges of the fp32 matrix-instruction kernel: tails in M, N and K (K not
+    a multiple of 16), both tile sizes, NaN around the operands."""
+    rng = np.random.default_rng(M + N + K)
+    X = rng.standard_normal((M, K)).astype(np.float32)
+    W = (rng.standard_normal((N, K)) * 0.05).astype(np.float32)
+
+    def placed(a):  # the matrix `shift` floats into a buffer of NaN
+        buf = torch.full((a.size + 64,), float("nan"), dtype=torch.float32, device=DEV)
+        buf[shift:shift + a.size] = to_dev(a, torch.float32).reshape(-1)
+        return buf[shift:shift + a.size].view(a.shape)
+
+    Y = torch.full((M + 1, N), float("nan"), dtype=torch.float32, device=DEV)
+    lp.op_gemm(placed(X), placed(W), Y[:M])
+    torch.cuda.synchronize()
+    assert torch.isnan(Y[M]).all()                    # nothing past the last row
+    ref = X.astype(np.float64) @ W.astype(np.float64).T
+    bound = 1e-5 * (np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64)).T) + 1e-12
+    assert np.all(np.abs(Y[:M].cpu().numpy() - ref) <= bound)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("rows,d,n_part", [(4, 256, 0), (64, 4096, 3), (7, 8192, 0), (33, 5120, 1)])
 def test_rmsnorm(dtype, rows, d, n_part):
