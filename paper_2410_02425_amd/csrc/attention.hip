@@ -657,185 +657,329 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const T *__restrict__
 }
 
 // 16-bit causal prefill attention on MFMA (flash-attention style).  A
-// workgroup owns 64 query rows of one (sequence, head); each wave owns 16 of
-// them.  Key blocks of 64 positions are staged in LDS (K as [key][dim], V
-// transposed as [dim][key], rows padded so the 16-byte fragment reads of a
-// wave fall in distinct banks) with the next block prefetched into registers
-// while the current one is used.  S = Q K^T and O += P V are 16x16x32 MFMAs,
-// the softmax is online (running max and sum per row, reduced across the 16
-// lanes of a row by DPP lane moves), and only the diagonal block needs the
-// causal mask.  The launch bound (at least two workgroups' worth of waves
-// per SIMD) makes the compiler keep the 128-dim kernel at 148 VGPRs, so three
-// waves share each SIMD and one wave's softmax runs under another's MFMAs.
-// Grid: (query tile, head, sequence), or with longest_first (head, sequence,
-// query tile) with the tiles walked from the last, so that the tiles with the
-// most key blocks are dispatched first and the short ones fill in behind them.
-template <typename T, int HD>
-__global__ __launch_bounds__(256, 2) void prefill_attn_mfma_kernel(const T *__restrict__ q, T *__restrict__ out,
-                                                                const int32_t *seq_start, const int32_t *seq_slot,
-                                                                KVCache kv, int layer, int n_heads,
-                                                                int longest_first) {
+// workgroup owns 32 QW query rows of one (sequence, head), 32 to a wave, and
+// walks the keys in blocks of 64.  Blocks are copied straight from the cache
+// into LDS (two stages per key group: the next block lands while the current
+// one is used), in the cache's own order (K [key][dim], V transposed
+// [dim][key]) with the 16-byte pieces of a row XOR-swizzled, by choosing the
+// address each lane copies from, so that the fragment reads below are free of
+// bank conflicts.
+//   S^T = K Q^T in 32x32x16 MFMAs: a lane holds one query's scores, so the
+//   softmax's maximum and sum run in the lane's own registers and meet its
+//   other half (lane ^ 32) once a block.  The K row that MFMA row i reads is i
+//   with bits 2 and 3 swapped: then the eight probabilities a lane holds of
+//   each 16 keys are consecutive keys, which is the B operand of
+//   O^T += V^T P^T, and P never leaves the registers.
+//   The running maximum is moved (and O and the sum rescaled) only where a
+//   score exceeds it by more than 8 in base-2 units: probabilities then stay
+//   within 2^8, well inside either 16-bit type, and the quotient is the same.
+// 32 rows a wave read half the LDS bytes per flop that 16 did (the 16-row
+// kernel needed 256 B a clock and CU, all that LDS delivers), and the vector
+// work of the softmax is what is left beside the MFMAs.  8B heads, fp16, 16-row
+// waves against this kernel: one prompt of 547 tokens 20.6 -> 15.5 us, 4,096
+// tokens 276 -> 169, three of 8,400 together 542 -> 328 (880 TFLOP/s, the
+// clock down to 1.8 GHz); 64 prompts of 600 640 -> 484.  Deeper staging (three
+// to five stages), the next block's scores or the output products interleaved
+// with the softmax by hand, and 64- or 256-row tiles all measured the same or
+// slower.
+// KG key groups: group k of the waves takes every KG-th key block with its own
+// stages, and the groups' (maximum, sum, O) meet in LDS at the end.
+// Grid: x = head, dealt so that the heads of one KV head run on one XCD and
+// share its L2; then with seq_major the query tiles and sequences, else the
+// sequences and query tiles; tiles from the last, so that those with the most
+// key blocks are dispatched first.
+__device__ __forceinline__ float half_swap_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_swap_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::v8 pack8(const float *p) {
+  typedef __typeof__((typename Mfma<T>::v8){}[0]) elem_t;
+  typename Mfma<T>::v8 v;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = (elem_t)p[j];
+  return v;
+}
+
+constexpr float PFA_SLACK = 8.f;  // base-2 units a score may exceed the running maximum by
+
+template <typename T, int HD, int QW, int KG>
+__global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const T *__restrict__ q,
+                                                                          T *__restrict__ out,
+                                                                          const int32_t *seq_start,
+                                                                          const int32_t *seq_slot, KVCache kv,
+                                                                          int layer, int n_heads, int seq_major) {
   typedef typename Mfma<T>::v8 v8;
-  constexpr int KS = HD / 32;                 // contraction steps over head_dim
-  constexpr int NT = HD / 16;                 // output tiles over head_dim
-  constexpr int KPAD = HD + 8;                // K row stride (elements)
-  constexpr int VPAD = 64 + 8;                // Vt row stride
-  constexpr int CH = 64 * HD * 2 / 16 / 256;  // 16-byte chunks per thread per block (K and V)
-  __shared__ T ks[64][KPAD];
-  __shared__ T vs[HD][VPAD];
-  __shared__ T pls[4][16][64 + 8];
-  const int qt = longest_first ? (int)gridDim.z - 1 - (int)blockIdx.z : (int)blockIdx.x;
-  const int h = longest_first ? (int)blockIdx.x : (int)blockIdx.y;
-  const int j = longest_first ? (int)blockIdx.y : (int)blockIdx.z;
+  constexpr int KS = HD / 16;            // contraction steps of S over head_dim
+  constexpr int NT = HD / 32;            // 32-dim tiles of O^T
+  constexpr int CK = HD / 8;             // 16-byte pieces of a K row
+  constexpr int PB = 64 * HD * 2;        // bytes of a K (or V) block
+  constexpr int STAGE = 2 * PB;
+  constexpr int ND = PB / 1024 / QW;     // 1 KB copies per wave and block, K and V each
+  __shared__ __attribute__((aligned(1024))) char lds[KG * 2 * STAGE];
+  static_assert(KG == 1 || (KG - 1) * QW * (NT * 16 + 2) * 256 <= KG * 2 * STAGE, "space of the group merge");
+  const int xh = blockIdx.x;
+  const int h = n_heads % 8 == 0 ? xh % 8 * (n_heads / 8) + xh / 8 : xh;
+  const int qt = (int)(seq_major ? gridDim.y - 1 - blockIdx.y : gridDim.z - 1 - blockIdx.z);
+  const int j = (int)(seq_major ? blockIdx.z : blockIdx.y);
   const int row0 = seq_start[j];
   const int len = seq_start[j + 1] - row0;
-  if (qt * 64 >= len) return;
+  if (qt * QW * 32 >= len) return;
   const int slot = seq_slot[j];
   const int g = h / (n_heads / kv.n_kv_heads);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int r16 = lane & 15, quad = lane >> 4, kq = quad * 8;
-  const int q0 = qt * 64 + wave * 16;  // first query position of this wave
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int kg = wave / QW, qw = wave % QW;
+  const int l32 = lane & 31, hh = lane >> 5;
+  const int q0 = qt * QW * 32 + qw * 32, qpos = q0 + l32;
 
-  v8 qa[KS];
+  // Q^T as the B operand: this lane's query, dims 16 k + 8 hh ..
+  v8 qb[KS];
   {
-    const int qp = min(q0 + r16, len - 1);
-    const T *qr = q + ((int64_t)(row0 + qp) * n_heads + h) * HD;
+    const T *qr = q + ((int64_t)(row0 + min(qpos, len - 1)) * n_heads + h) * HD + hh * 8;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) qa[k] = load8<T>(qr + k * 32 + kq);
+    for (int k = 0; k < KS; ++k) qb[k] = load8<T>(qr + k * 16);
   }
-  floatx4_t oacc[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) oacc[nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  float mrow[4], lrow[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    mrow[i] = -INFINITY;
-    lrow[i] = 0.f;
-  }
-  // scores in base-2 units: e^x = 2^(x log2 e), with the factor folded into
-  // the scale, so each exponential is one v_exp_f32
-  const float scale = rsqrtf((float)HD) * 1.44269504088896341f;
-  const int nblk = min(qt + 1, (len + 63) / 64);  // causal: key blocks up to the diagonal
+  const int nblk = min((qt * QW * 32 + QW * 32 + 63) / 64, (len + 63) / 64);  // causal: up to the diagonal
+  const int nit = (nblk + KG - 1) / KG;
 
-  // staging: chunk c of a block -> K: key c / (HD/8), dims (c % (HD/8)) * 8;
-  //                               Vt: dim c / 8, keys (c % 8) * 8
-  u32x4_tt kr[CH], vr[CH];
-  auto fetch = [&](int kb) __attribute__((always_inline)) {
-    const int64_t base = kv_block_base(kv, layer, slot, kb * 64, g);
-    const u32x4_tt *kp = (const u32x4_tt *)((const T *)kv.k + base);
-    const u32x4_tt *vp = (const u32x4_tt *)((const T *)kv.v + base);
+  // Byte offsets of the sequence's cache blocks (layer and head included): lane
+  // i holds that of block win + i, and the wave reads them back with readlane.
+  const int32_t *bt = kv.block_table + (int64_t)slot * kv.max_blocks;
+  const int64_t head0 = ((int64_t)layer * kv.n_blocks * kv.n_kv_heads + g) * PB;
+  const int64_t blk_step = (int64_t)kv.n_kv_heads * PB;
+  int win = 0, off_lo, off_hi;
+  auto window = [&]() __attribute__((always_inline)) {
+    const int64_t off = head0 + bt[min(win + lane, nblk - 1)] * blk_step;
+    off_lo = (int)off;
+    off_hi = (int)(off >> 32);
+    // used here, so that the wait for the load stands here and not at every
+    // step's readlane
+    asm volatile("" : "+v"(off_lo), "+v"(off_hi));
+  };
+  window();
+  // Copies of this wave: K rows (1024 / (2 HD) a copy) and V rows (8 a copy);
+  // lane l's 16 bytes land at piece l of the copy.
+  constexpr int KR = 1024 / (HD * 2);
+  const uint32_t lds0 = lds_addr(lds) + kg * 2 * STAGE + qw * ND * 1024;
+  const int kcr = lane / CK, kcp = lane % CK, vcr = lane >> 3, vcp = lane & 7;
+  auto swz = [](int row) __attribute__((always_inline)) { return CK == 16 ? row & 15 : (row >> 1) & 7; };
+  uint32_t ko[ND], vo[ND];  // byte offsets inside a block
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      kr[c] = kp[tid + c * 256];
-      vr[c] = vp[tid + c * 256];
+  for (int c = 0; c < ND; ++c) {
+    const int n = qw * ND + c, kr = n * KR + kcr, vr = n * 8 + vcr;
+    ko[c] = kr * HD * 2 + (kcp ^ swz(kr)) * 16;
+    vo[c] = vr * KV_BLOCK * 2 + (vcp ^ ((vr >> 1) & 7)) * 16;
+  }
+  auto issue = [&](int it) __attribute__((always_inline)) {
+    const int kb = it * KG + kg;
+    if (kb >= nblk) return;
+    if (kb >= win + 64) {
+      win = kb;
+      window();
+    }
+    const int64_t off = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(off_hi, kb - win) << 32) |
+                                  (uint32_t)__builtin_amdgcn_readlane(off_lo, kb - win));
+    const uint32_t st = lds0 + (it & 1) * STAGE;
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      dma16s((const char *)kv.k + off, ko[c], st + c * 1024);
+      dma16s((const char *)kv.v + off, vo[c], st + PB + c * 1024);
     }
   };
-  fetch(0);
-  for (int kb = 0; kb < nblk; ++kb) {
-    __syncthreads();  // previous block fully consumed
-    const int kvalid = len - kb * 64;  // keys of this block inside the sequence
+
+  floatx16_t o[NT];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int e = tid + c * 256;
-      *(u32x4_tt *)&ks[e / (HD / 8)][(e % (HD / 8)) * 8] = kr[c];
-      // cache entries past the sequence end are stale or uninitialised; their
-      // softmax weight is 0 but 0 * NaN is not, so they become zeros here
-      u32x4_tt v = vr[c];
-      const int key0 = (e % 8) * 8;
-      if (key0 + 8 > kvalid) {
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint32_t lo = key0 + 2 * w < kvalid ? 0xFFFFu : 0u;
-          const uint32_t hi = key0 + 2 * w + 1 < kvalid ? 0xFFFF0000u : 0u;
-          v[w] &= (lo | hi);
+    for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
+  // running maximum (raw scores), the score past which it moves, its base-2
+  // value; this half's share of the sum
+  float mref = -INFINITY, mlim = -INFINITY, mc = 0.f, lsum = 0.f;
+  const float c2 = rsqrtf((float)HD) * 1.44269504088896341f;
+  // fragment addresses: K row with bits 2 and 3 swapped, V row l32 (+ 32 t)
+  const int krow = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
+  const int kfb = krow * HD * 2, kfx = (hh ^ swz(krow)) << 4;
+  const int vfb = l32 * KV_BLOCK * 2, vfx = (hh ^ ((l32 >> 1) & 7)) << 4;
+
+  issue(0);
+  for (int it = 0; it < nit; ++it) {
+    // this wave's copies of the block have landed; after the barrier everyone's
+    // have, and the stage of the block before is free
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (it == nit - 1 && nblk * 64 > len) {
+      // the sequence ends inside the last block: V entries past it are stale
+      // or uninitialised, their weight is 0 but 0 * NaN is not
+      if ((nblk - 1) % KG == kg) {
+        const int kvalid = len - (nblk - 1) * 64;
+        char *vs = lds + kg * 2 * STAGE + (it & 1) * STAGE + PB;
+        for (int e = qw * 64 + lane; e < HD * 8; e += QW * 64) {
+          const int row = e >> 3, key0 = ((e & 7) ^ ((row >> 1) & 7)) * 8;
+          if (key0 + 8 > kvalid) {
+            u32x4_tt v = *(const u32x4_tt *)(vs + e * 16);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+              const uint32_t lo = key0 + 2 * w < kvalid ? 0xFFFFu : 0u;
+              const uint32_t hi = key0 + 2 * w + 1 < kvalid ? 0xFFFF0000u : 0u;
+              v[w] &= (lo | hi);
+            }
+            *(u32x4_tt *)(vs + e * 16) = v;
+          }
         }
       }
-      *(u32x4_tt *)&vs[e / 8][key0] = v;
+      __syncthreads();
+    }
+    if (it + 1 < nit) issue(it + 1);
+    const int kb = it * KG + kg;
+    if (kb >= nblk || kb * 64 > q0 + 31) continue;  // no block, or wholly past this wave's queries
+    const char *ks = lds + kg * 2 * STAGE + (it & 1) * STAGE, *vs = ks + PB;
+    floatx16_t s[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const v8 a = *(const v8 *)(ks + kfb + t * 32 * HD * 2 + (kfx ^ (k << 5)));
+        s[t] = Mfma<T>::m32(a, qb[k], s[t]);
+      }
+    }
+    // s[t][r]: key 32 t + 16 (r / 8) + 8 hh + r % 8 of the block
+    if (kb * 64 + 63 > q0) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kb * 64 + t * 32 + (r >> 3) * 16 + hh * 8 + (r & 7) > qpos) s[t][r] = -INFINITY;
+    }
+    float mx = s[0][0];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[t][r]);
+    mx = half_swap_max(mx);
+    if (__any(mx > mlim)) {
+      const float nm = fmaxf(mref, mx);
+      const float corr = nm == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mref - nm) * c2);
+      mref = nm;
+      mlim = nm + PFA_SLACK / c2;
+      mc = nm == -INFINITY ? 0.f : nm * c2;  // a row that has seen no key yet
+      lsum *= corr;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][r] *= corr;
+    }
+    v8 pb[4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        float p[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          p[r] = __builtin_amdgcn_exp2f(fmaf(s[t][u * 8 + r], c2, -mc));
+          lsum += p[r];
+        }
+        pb[t * 2 + u] = pack8<T>(p);
+      }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const v8 a = *(const v8 *)(vs + vfb + t * 32 * KV_BLOCK * 2 + (vfx ^ (k << 5)));
+        o[t] = Mfma<T>::m32(a, pb[k], o[t]);
+      }
+  }
+  if constexpr (KG > 1) {
+    // groups 1.. hand (O, maximum, sum) to group 0, lane by lane
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    constexpr int REC = NT * 16 + 2;
+    float *mrg = (float *)lds;
+    if (kg > 0) {
+      float *w = mrg + ((kg - 1) * QW + qw) * REC * 64 + lane;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) w[(t * 16 + r) * 64] = o[t][r];
+      w[NT * 16 * 64] = mref;
+      w[(NT * 16 + 1) * 64] = lsum;
     }
     __syncthreads();
-    if (kb + 1 < nblk) fetch(kb + 1);
-    // S = Q K^T over the 64 keys of this block
-    floatx4_t sacc[4];
+    if (kg > 0) return;
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      sacc[nt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k = 1; k < KG; ++k) {
+      const float *w = mrg + ((k - 1) * QW + qw) * REC * 64 + lane;
+      const float m1 = w[NT * 16 * 64], l1 = w[(NT * 16 + 1) * 64];
+      const float nm = fmaxf(mref, m1);
+      const float f0 = nm == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mref - nm) * c2);
+      const float f1 = nm == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m1 - nm) * c2);
+      mref = nm;
+      lsum = lsum * f0 + l1 * f1;
 #pragma unroll
-      for (int k = 0; k < KS; ++k) sacc[nt] = Mfma<T>::m16(qa[k], load8<T>(&ks[nt * 16 + r16][k * 32 + kq]), sacc[nt]);
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][r] = o[t][r] * f0 + w[(t * 16 + r) * 64] * f1;
     }
-    // online softmax: row 4*quad + i of this wave, keys nt*16 + r16
-    const bool diag = kb == nblk - 1;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int qpos = q0 + 4 * quad + i;
-      float mx = mrow[i];
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int kpos = kb * 64 + nt * 16 + r16;
-        const bool ok = !diag || (kpos <= qpos && kpos < len);
-        sacc[nt][i] = ok ? sacc[nt][i] * scale : -INFINITY;
-        mx = fmaxf(mx, sacc[nt][i]);
-      }
-      mx = row16_max(mx);
-      // rows past the sequence end see no valid key: keep them finite
-      const float mref = (mx == -INFINITY) ? 0.f : mx;
-      const float corr = __builtin_amdgcn_exp2f(mrow[i] - mref);
-      float t = 0.f;
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const float p = __builtin_amdgcn_exp2f(sacc[nt][i] - mref);
-        sacc[nt][i] = p;
-        t += p;
-      }
-      t = row16_sum(t);
-      lrow[i] = lrow[i] * corr + t;
-      mrow[i] = mx;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) oacc[nt][i] *= corr;
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) pls[wave][4 * quad + i][nt * 16 + r16] = Act<T>::st(sacc[nt][i]);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    v8 pa[2];
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) pa[kk] = load8<T>(&pls[wave][r16][kk * 32 + kq]);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-        oacc[nt] = Mfma<T>::m16(pa[kk], load8<T>(&vs[nt * 16 + r16][kk * 32 + kq]), oacc[nt]);
   }
-  // rows 4*quad + i, dims nt*16 + r16
+  // o[t][r]: dim 32 t + 8 (r / 4) + 4 hh + r % 4 of this lane's query
+  const float inv = 1.0f / half_swap_sum(lsum);
+  if (qpos < len) {
+    T *orow = out + ((int64_t)(row0 + qpos) * n_heads + h) * HD + hh * 4;
+    const bool al8 = ((uintptr_t)out & 7) == 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int qpos = q0 + 4 * quad + i;
-    if (qpos < len) {
-      const float inv = 1.0f / lrow[i];
-      T *orow = out + ((int64_t)(row0 + qpos) * n_heads + h) * HD;
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) orow[nt * 16 + r16] = Act<T>::st(oacc[nt][i] * inv);
-    }
+      for (int r4 = 0; r4 < 4; ++r4) {
+        T v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = Act<T>::st(o[t][r4 * 4 + e] * inv);
+        T *dst = orow + t * 32 + r4 * 8;
+        if (al8)
+          *(uint2 *)dst = __builtin_bit_cast(uint2, *(const uint2 *)v);
+        else
+          for (int e = 0; e < 4; ++e) dst[e] = v[e];
+      }
   }
 }
 
-// Steps of at most this many prompts dispatch the longest query tiles first:
-// with few prompts the tiles of the most key blocks bound the launch (1.1-1.7x
-// faster for one to three prompts of 547-4,000 tokens).  With many, walking
-// each (prompt, head)'s tiles together keeps its keys and values in the L2
-// (64 prompts of 43k tokens: 0.70 against 0.81 ms the other way).
+// Steps of at most this many prompts dispatch the longest query tiles of all
+// prompts first; with more, each prompt's tiles run together, so that its keys
+// and values stay in the L2.
 constexpr int PF_ATTN_LONGEST_FIRST_MAX_SEQ = 4;
+template <typename T, int HD, int QW, int KG>
+static void launch_prefill_mfma(const T *q, T *out, const int32_t *seq_start, const int32_t *seq_slot, int n_seq,
+                                int max_len, const KVCache &kv, int layer, int n_heads, hipStream_t s) {
+  const int tiles = (max_len + QW * 32 - 1) / (QW * 32);
+  const int seq_major = n_seq > PF_ATTN_LONGEST_FIRST_MAX_SEQ;
+  const dim3 grid = seq_major ? dim3(n_heads, tiles, n_seq) : dim3(n_heads, n_seq, tiles);
+  prefill_attn_mfma_kernel<T, HD, QW, KG><<<grid, QW * KG * 64, 0, s>>>(q, out, seq_start, seq_slot, kv, layer,
+                                                                         n_heads, seq_major);
+}
 
 template <typename T, int HD>
-static void launch_prefill_hd(dim3 grid, const T *q, T *out, const int32_t *seq_start, const int32_t *seq_slot,
-                              const KVCache &kv, int layer, int n_heads, hipStream_t s) {
+static void launch_prefill_hd(const T *q, T *out, const int32_t *seq_start, const int32_t *seq_slot, int n_seq,
+                              int max_len, const KVCache &kv, int layer, int n_heads, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
-    if ((int)grid.z <= PF_ATTN_LONGEST_FIRST_MAX_SEQ)
-      prefill_attn_mfma_kernel<T, HD><<<dim3(grid.y, grid.z, grid.x), 256, 0, s>>>(q, out, seq_start, seq_slot, kv,
-                                                                                   layer, n_heads, 1);
+    // Two key groups for one prompt whose workgroups are too few for two on
+    // every CU but enough to use most CUs: each CU's second set of waves then
+    // comes from the key groups, and the longest tile walks half its blocks
+    // (8B heads: 888 tokens, 224 workgroups, 23.7 -> 22.3 us; 1,300 tokens, 352,
+    // 34.6 -> 30.2; 1,700 tokens, 448, 44.7 -> 42.2).  Below, the merge costs
+    // what it saves (400 tokens, 128: 13.0 against 13.1; 234 tokens: 10.0
+    // against 11.1); above, two workgroups a CU overlap better (4,096 tokens:
+    // 169 against 187), and with several prompts the grid's upper bound says
+    // little about the live tiles (3 x 400 tokens: 16.5 against 19.2).
+    const int64_t wgs = (int64_t)((max_len + 127) / 128) * n_heads;
+    if (n_seq == 1 && wgs >= 160 && wgs <= 448)
+      launch_prefill_mfma<T, HD, 4, 2>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
     else
-      prefill_attn_mfma_kernel<T, HD><<<grid, 256, 0, s>>>(q, out, seq_start, seq_slot, kv, layer, n_heads, 0);
+      launch_prefill_mfma<T, HD, 4, 1>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
   } else {
+    const dim3 grid((max_len + 63) / 64, n_heads, n_seq);
     prefill_attn_kernel<T, HD><<<grid, 256, 0, s>>>(q, out, seq_start, seq_slot, kv, layer, n_heads);
   }
 }
@@ -845,11 +989,10 @@ void launch_prefill_attention(const T *q, T *out, const int32_t *seq_start, cons
                               int n_seq, int max_len, const KVCache &kv, int layer, int n_heads,
                               hipStream_t s) {
   if (n_seq <= 0) return;
-  dim3 grid((max_len + 63) / 64, n_heads, n_seq);
   if (kv.head_dim == 128)
-    launch_prefill_hd<T, 128>(grid, q, out, seq_start, seq_slot, kv, layer, n_heads, s);
+    launch_prefill_hd<T, 128>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
   else if (kv.head_dim == 64)
-    launch_prefill_hd<T, 64>(grid, q, out, seq_start, seq_slot, kv, layer, n_heads, s);
+    launch_prefill_hd<T, 64>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
 }
 
 #define INST(T)                                                                                     \

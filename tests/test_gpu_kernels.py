@@ -453,6 +453,44 @@ def test_prefill_attention(dtype, Hq, Hkv, hd, lens):
         r0 += n
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,hd,lens,shift", [
+    ("f16", 8, 8, 128, [31, 32, 33, 127, 128, 129], 0),     # edges of a wave's 32 and a tile's 128 rows
+    ("bf16", 4, 2, 64, [63, 64, 65, 1], 0),                 # block edges, heads not a multiple of 8
+    ("f16", 32, 8, 128, [641], 0),                          # 192 workgroups: two key groups, an odd block count
+    ("bf16", 64, 8, 64, [385], 0),                          # the same at head_dim 64, 256 workgroups, group of 8
+    ("f16", 2, 1, 128, [4230], 0),                          # more than 64 cache blocks
+    ("f16", 64, 32, 128, [260], 1),                         # out off 8 bytes: element stores; two key groups
+])
+def test_prefill_attention_tiles(dtype, Hq, Hkv, hd, lens, shift):
+    """Edges of the prefill attention's tiles, key groups and copies, with every
+    cache entry past a sequence's end NaN."""
+    rng = np.random.default_rng(sum(lens) + Hq)
+    tdt = HALF[dtype]
+    (kc, vt, bt), Ks, Vs = make_paged_cache(rng, lens, Hkv, hd, tdt)
+    for j, n in enumerate(lens):
+        if n % 64:
+            b = int(bt[j, n // 64])
+            kc[b, :, n % 64:] = float("nan")
+            vt[b, :, :, n % 64:] = float("nan")
+    rows = sum(lens)
+    q = bf16_values(rng, (rows, Hq, hd))
+    buf = torch.full((rows * Hq * hd + 64,), float("nan"), dtype=tdt, device=DEV)
+    out = buf[shift:shift + rows * Hq * hd].view(rows, Hq, hd)
+    seq_start = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device=DEV)
+    seq_slot = torch.arange(len(lens), dtype=torch.int32, device=DEV)
+    lp.op_prefill_attention(to_dev(q, tdt), out, kc, vt, bt, seq_start, seq_slot, max(lens), Hkv)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    assert torch.isnan(buf[shift + rows * Hq * hd:]).all() and torch.isnan(buf[:shift]).all()
+    r0 = 0
+    for j, n in enumerate(lens):
+        args = (q[r0:r0 + n].astype(np.float64), Ks[j].astype(np.float64))
+        ref = T.attention(*args, Vs[j].astype(np.float64), np.arange(n), np.arange(n), Hkv)
+        mag = T.attention(*args, np.abs(Vs[j].astype(np.float64)), np.arange(n), np.arange(n), Hkv)
+        assert np.all(np.abs(got[r0:r0 + n] - ref) <= attention_tol(dtype, ref, mag)), j
+        r0 += n
+
+
 def test_zero_row_calls_through_the_binding():
     """Empty device tensors (null data pointers) through the binding: nothing
     is launched and the outputs of other calls are untouched."""
