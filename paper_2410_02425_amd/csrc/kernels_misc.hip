@@ -1,5 +1,7 @@
 // Embedding gather, RMSNorm (with split-K residual folding), greedy argmax and
 // the device-side weight generator.
+#include <type_traits>
+
 #include "device.hpp"
 
 namespace lp {
@@ -145,56 +147,119 @@ void launch_rmsnorm(float *x, const float *part, int n_part, int64_t part_stride
 
 // ------------------------------------------------------------------ argmax
 
-// One workgroup of 1024 threads per row, 16-byte loads, eight of them
-// requested before any is used (a row then costs four memory round trips, not
-// thirty-two).  Merges prefer the larger value, then the lower index: a total
-// order, so the result does not depend on the order of the merges.
-__device__ __forceinline__ void argmax_merge(float &bv, int &bi, float ov, int oi) {
-  if (ov > bv || (ov == bv && oi < bi)) {
-    bv = ov;
-    bi = oi;
+// Walks over a row of logits (argmax and sampling).  A workgroup of ROW_W
+// waves owns a row and each wave a contiguous part of it, ROW_STEP elements a
+// step (16 bytes a lane) and eight steps' loads requested before any is used,
+// so a 128,256-entry row costs four memory round trips.  One CU's vector
+// units, not its loads, bound such a pass (a row is 2,004 wave instructions
+// for every instruction an element takes, 0.8 us on four SIMDs), so a full
+// batch of steps runs without bounds checks.
+constexpr int ROW_W = 16, ROW_T = ROW_W * 64, ROW_STEP = 256, ROW_U = 8;
+struct RowPart {
+  const float *row;
+  int beg, end;  // this wave's elements
+  bool vec;      // the row's 16-byte pieces are aligned
+};
+__host__ __device__ inline int row_chunk(int V) { return (V + ROW_W * ROW_STEP - 1) / (ROW_W * ROW_STEP) * ROW_STEP; }
+__device__ __forceinline__ RowPart row_part(const float *logits, int64_t ld, int m, int V) {
+  const int chunk = row_chunk(V), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int beg = min(V, w * chunk);
+  return {logits + (int64_t)m * ld, beg, min(V, beg + chunk), ld % 4 == 0 && ((uintptr_t)logits & 15) == 0};
+}
+__device__ __forceinline__ float4 row_load4(const RowPart &R, int c, float fill) {
+  float4 v;
+  v.x = c < R.end ? R.row[c] : fill;
+  v.y = c + 1 < R.end ? R.row[c + 1] : fill;
+  v.z = c + 2 < R.end ? R.row[c + 2] : fill;
+  v.w = c + 3 < R.end ? R.row[c + 3] : fill;
+  return v;
+}
+// f(index of the first element, four logits, how many of them exist) for this
+// lane's elements, g(batch) after every ROW_U steps.  All lanes are active in
+// every call.
+template <typename F, typename G>
+__device__ __forceinline__ void row_walk(const RowPart &R, F f, G g) {
+  const int lane = threadIdx.x & 63;
+  int batch = 0;
+  for (int c0 = R.beg; c0 < R.end; c0 += ROW_U * ROW_STEP, ++batch) {
+    if (R.vec && c0 + ROW_U * ROW_STEP <= R.end) {
+      float4 v[ROW_U];
+#pragma unroll
+      for (int u = 0; u < ROW_U; ++u) v[u] = *(const float4 *)(R.row + c0 + u * ROW_STEP + lane * 4);
+#pragma unroll
+      for (int u = 0; u < ROW_U; ++u) f(c0 + u * ROW_STEP + lane * 4, v[u], std::integral_constant<int, 4>());
+    } else {
+      for (int u = 0; u < ROW_U; ++u) {
+        const int c = c0 + u * ROW_STEP + lane * 4;
+        f(c, row_load4(R, c, -INFINITY), min(4, max(0, R.end - c)));
+      }
+    }
+    g(batch);
   }
 }
 
-__global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ logits, int64_t ld, int V,
-                                                      const int32_t *out_slot, int32_t *slot_tok, int32_t *tok_log) {
-  __shared__ float sv[16];
-  __shared__ int si[16];
-  const int m = blockIdx.x;
-  const float *row = logits + (int64_t)m * ld;
-  float best = -INFINITY;
-  int bi = 0x7fffffff;
-  const int v4 = ((ld & 3) == 0) ? V >> 2 : 0;
-  constexpr int U = 8;
-  for (int c0 = threadIdx.x; c0 < v4; c0 += 1024 * U) {
-    float4 q[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) q[u] = ((const float4 *)row)[min(c0 + u * 1024, v4 - 1)];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = c0 + u * 1024;
-      if (c < v4) {
-        argmax_merge(best, bi, q[u].x, 4 * c);
-        argmax_merge(best, bi, q[u].y, 4 * c + 1);
-        argmax_merge(best, bi, q[u].z, 4 * c + 2);
-        argmax_merge(best, bi, q[u].w, 4 * c + 3);
-      }
-    }
-  }
-  for (int c = 4 * v4 + threadIdx.x; c < V; c += 1024) argmax_merge(best, bi, row[c], c);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(best, o, 64);
-    const int oi = __shfl_xor(bi, o, 64);
-    argmax_merge(best, bi, ov, oi);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    sv[threadIdx.x >> 6] = best;
-    si[threadIdx.x >> 6] = bi;
-  }
+// This lane's largest logit, where its first 16-byte piece that holds it
+// starts, and whether it met a NaN (which no comparison picks).
+struct RowBest {
+  float v;
+  int c;
+  bool nan;
+};
+__device__ __forceinline__ RowBest row_best(const RowPart &R) {
+  RowBest b{-INFINITY, R.beg, false};
+  row_walk(
+      R,
+      [&](int c, const float4 &v, auto) {
+        const float m = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+        b.nan |= __builtin_isunordered(v.x, v.y) | __builtin_isunordered(v.z, v.w);
+        if (m > b.v) {
+          b.v = m;
+          b.c = c;
+        }
+      },
+      [](int) {});
+  return b;
+}
+// The row's largest logit, in every thread.
+__device__ __forceinline__ float row_max(const RowBest &b, float (&red)[ROW_W]) {
+  const float w = wave_max(b.v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
   __syncthreads();
+  return row16_max(red[threadIdx.x & (ROW_W - 1)]);
+}
+// The lowest index that holds mx (0x7fffffff: none, a row of NaN only), in
+// every thread.
+__device__ __forceinline__ int row_first(const RowPart &R, const RowBest &b, float mx, int (&red)[ROW_W]) {
+  int idx = 0x7fffffff;
+  if (mx == -INFINITY) {
+    for (int c = R.beg + (int)(threadIdx.x & 63); c < R.end; c += 64)
+      if (R.row[c] == mx) {
+        idx = c;
+        break;
+      }
+  } else if (b.v == mx) {
+#pragma unroll
+    for (int e = 3; e >= 0; --e)
+      if (b.c + e < R.end && R.row[b.c + e] == mx) idx = b.c + e;
+  }
+  idx = (int)wave_min_u32((uint32_t)idx);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = idx;
+  __syncthreads();
+  return (int)wave_min_u32((uint32_t)red[threadIdx.x & (ROW_W - 1)]);
+}
+
+// One workgroup per row: the maximum, then the lowest index that holds it,
+// found again in the one piece its lane remembers.  64 rows of 128,256: 15.7
+// -> 8.7 us (an index was merged with every element before).
+__global__ __launch_bounds__(ROW_T) void argmax_kernel(const float *__restrict__ logits, int64_t ld, int V,
+                                                       const int32_t *out_slot, int32_t *slot_tok, int32_t *tok_log) {
+  __shared__ float sv[ROW_W];
+  __shared__ int si[ROW_W];
+  const int m = blockIdx.x;
+  const RowPart R = row_part(logits, ld, m, V);
+  const RowBest b = row_best(R);
+  const int bi = row_first(R, b, row_max(b, sv), si);
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) argmax_merge(best, bi, sv[w], si[w]);
     if (out_slot) slot_tok[out_slot[m]] = bi;
     tok_log[m] = bi;
   }
@@ -203,7 +268,7 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
 void launch_argmax(const float *logits, int64_t ld, int M, int V, const int32_t *out_slot, int32_t *slot_tok,
                    int32_t *tok_log, hipStream_t s) {
   if (M <= 0) return;
-  argmax_kernel<<<M, 1024, 0, s>>>(logits, ld, V, out_slot, slot_tok, tok_log);
+  argmax_kernel<<<M, ROW_T, 0, s>>>(logits, ld, V, out_slot, slot_tok, tok_log);
 }
 
 // ------------------------------------------------------------------ weight generator
@@ -243,21 +308,33 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
 //  * draw: u24 = the first Philox4x32-10 output word (key, counter as given)
 //    shifted right by 8; r = floor(Z_kept * u24 / 2^24); the token is the kept
 //    candidate, in vocabulary order, whose cumulative weight interval holds r.
-// One workgroup per row.  The row is read in full at most five times: the
-// maximum (with the first top-k level), the top-k bin's elements, the weight
-// total (with the first top-p level), the top-p bin's elements, and the draw.
-// The remaining radix levels run over those elements held in LDS (a full-row
-// pass per level only when a bin holds more than SP_CAP elements).  When top-k
-// leaves at most SP_DRAW candidates, their weights and the draw stay in LDS.
-
+// One workgroup per row; vector work per element bounds it (see the walk
+// above), so the row is passed over as few times as the parameters allow:
+//  * the maximum, each lane's own maximum kept;
+//  * top_k <= SP_FASTK: at least top_k lanes hold a maximum of at least L, the
+//    top_k-th largest of them to within a histogram bin, so only the lanes
+//    that reach L hold candidates and only those read their elements again;
+//    larger top_k, rows with a NaN and rows whose list overflows select on
+//    histograms over the whole row;
+//  * no top_p: one pass adds up weights per 2,048 elements (a piece), which
+//    gives the total and, by a scan, the piece that holds the draw;
+//  * top_p: one pass for the total and the masses of log-scale weight bins,
+//    one that adds up the pieces of everything heavier than the chosen bin and
+//    lists that bin's elements, which the remaining levels refine in LDS.
+// Candidate sets of at most SP_SMALL are settled by direct sums.  64 rows of
+// 128,256 logits: greedy 23.7 -> 9.6 us, temperature 82.7 -> 26.6, top-k 40
+// 68.0 -> 28.3, top-p 0.9 157 -> 75.6, top-k 50 with top-p 0.95 90.5 -> 33.5.
 __device__ __forceinline__ uint32_t order_key(float x) {
   const uint32_t b = __float_as_uint(x);
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+// A weight before and after the floor.
+__device__ __forceinline__ float f_weight(float l, float mx, float inv_t) {
+  return __expf((l - mx) * inv_t) * 1099511627776.0f;  // 2^40; exp <= 1
+}
 __device__ __forceinline__ uint64_t q_weight(float l, float mx, float inv_t) {
-  const float w = __expf((l - mx) * inv_t);
-  return (uint64_t)(w * 1099511627776.0f);  // 2^40; w <= 1
+  return (uint64_t)f_weight(l, mx, inv_t);
 }
 
 // (a * b) >> 24 for a < 2^58, b < 2^25, rounded up when `up`
@@ -268,12 +345,15 @@ __device__ __forceinline__ uint64_t mul_shift24(uint64_t a, uint64_t b, bool up)
   return r;
 }
 
-constexpr int SP_T = 1024;     // threads per row
+constexpr int SP_T = ROW_T;    // threads per row
 constexpr int SP_NB = 2048;    // bins of a radix level (11 bits)
 constexpr int SP_CAP = 8192;   // values held in LDS after a compaction
 constexpr int SP_DRAW = 1024;  // kept candidates drawn in LDS (one per thread)
-// the full-row draw keeps a mass per 256 elements in the SP_CAP list
-static_assert((int64_t)SP_CAP * 256 >= SAMPLE_MAX_V, "sampling rows longer than the draw's piece list");
+constexpr int SP_FASTK = 512;  // largest top_k selected through the lanes' maxima
+constexpr int SP_SMALL = 256;  // candidates settled by direct sums over the list
+constexpr int SP_PIECE = ROW_U * ROW_STEP;  // elements per piece of the draw: one batch of a wave
+static_assert((int64_t)SP_T * SP_PIECE >= SAMPLE_MAX_V && SAMPLE_MAX_V % (ROW_W * SP_PIECE) == 0,
+              "one piece of the draw per thread");
 
 struct SampleLds {
   uint64_t hist[SP_NB];
@@ -281,10 +361,12 @@ struct SampleLds {
   int32_t li[SP_CAP];      // its vocabulary index
   uint64_t cq[SP_DRAW];    // candidates of an LDS draw: weight
   int32_t ci[SP_DRAW];     // ... and index
+  uint64_t pm[SP_T];       // kept mass per piece
   uint64_t red[16];
   uint64_t sel[4];
-  float fmax[16];
-  int imax[16];
+  float fmax[ROW_W];
+  int imax[ROW_W];
+  uint32_t kred[ROW_W];
   int n_list, n_cand, found, pick;
 };
 
@@ -294,24 +376,14 @@ __device__ __forceinline__ float key_float(uint32_t k) {
 
 // inclusive scan of v over the block's threads (thread order), and the total
 __device__ uint64_t sp_scan(uint64_t v, uint64_t *red, uint64_t &total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint64_t x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t t = __shfl_up(x, o, 64);
-    if (lane >= o) x += t;
-  }
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const uint64_t x = wave_scan(v);
   __syncthreads();
   if (lane == 63) red[w] = x;
   __syncthreads();
-  uint64_t base = 0;
-  total = 0;
-  for (int i = 0; i < 16; ++i) {
-    const uint64_t r = red[i];
-    if (i < w) base += r;
-    total += r;
-  }
-  return base + x;
+  const uint64_t waves = row16_scan(red[lane & 15]);
+  total = readlane_u64(waves, 15);
+  return x + (w ? readlane_u64(waves, w - 1) : 0);
 }
 
 // Radix level selection over hist[0..nb): the largest bin b >= 1 whose mass
@@ -353,6 +425,10 @@ __device__ __forceinline__ int sp_qbin(uint64_t q) {
   const int e = 63 - __clzll((long long)q);
   return 32 + 32 * (e - 5) + (int)((q >> (e - 5)) & 31);
 }
+// the same from the weight before the floor (which moves no bit that it reads)
+__device__ __forceinline__ int sp_fbin(float f) {
+  return f < 64.f ? (int)f : (int)(__float_as_uint(f) >> 18) - (32 * (127 + 5) - 32);
+}
 // lowest weight of bin b and the number of its free low bits
 __device__ __forceinline__ void sp_qbin_range(int b, uint64_t &lo, int &bits) {
   if (b < 64) {
@@ -390,119 +466,214 @@ __device__ __forceinline__ int sp_append(bool pred, int *counter) {
   return pred ? base + __popcll(mask & ((1ull << lane) - 1ull)) : -1;
 }
 
-// Calls f(index, logit, valid) for every element of the row, four per thread
-// and step, all lanes active in every step (valid false past V).  Eight steps'
-// loads are issued before any element is used.
-__device__ __forceinline__ float4 sp_load4(const float *row, int c, int V, bool vec) {
-  float4 v;
-  if (vec && c + 3 < V) {
-    v = *(const float4 *)(row + c);
-  } else {
-    v.x = c < V ? row[c] : 0.f;
-    v.y = c + 1 < V ? row[c + 1] : 0.f;
-    v.z = c + 2 < V ? row[c + 2] : 0.f;
-    v.w = c + 3 < V ? row[c + 3] : 0.f;
-  }
-  return v;
+// smallest of the threads' v, in every thread
+__device__ uint32_t sp_min(uint32_t v, uint32_t (&red)[ROW_W]) {
+  v = wave_min_u32(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return wave_min_u32(red[threadIdx.x & (ROW_W - 1)]);
 }
 
+__device__ __forceinline__ float at4(const float4 &v, int e) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; }
+
+// f(index, logit, valid) for every element
 template <typename F>
-__device__ __forceinline__ void sp_row(const float *row, int V, bool vec, F f) {
-  constexpr int U = 8;
-  const int steps = (V + 4 * SP_T - 1) / (4 * SP_T);
-  for (int s0 = 0; s0 < steps; s0 += U) {
-    float4 v[U];
+__device__ __forceinline__ void sp_row(const RowPart &R, F f) {
+  row_walk(
+      R,
+      [&](int c, const float4 &v, auto n) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = sp_load4(row, ((s0 + u) * SP_T + threadIdx.x) * 4, V, vec);
+        for (int e = 0; e < 4; ++e) f(c + e, at4(v, e), e < n);
+      },
+      [](int) {});
+}
+
+// The weights of the row's candidates (order key at least kmin; FILT: kmin is
+// not 0): f(index, weight before the floor, weight) for each, and per piece the
+// sum of what f returns, into S.pm when PIECES.
+template <bool FILT, bool PIECES, typename F>
+__device__ __forceinline__ void sp_weights(SampleLds &S, const RowPart &R, int V, uint32_t kmin, float mx, float inv_t,
+                                           F f) {
+  uint64_t acc = 0;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int per = (row_chunk(V) + SP_PIECE - 1) / SP_PIECE;  // pieces a wave
+  row_walk(
+      R,
+      [&](int c, const float4 &v, auto n) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = ((s0 + u) * SP_T + threadIdx.x) * 4;
-      f(c, v[u].x, c < V);
-      f(c + 1, v[u].y, c + 1 < V);
-      f(c + 2, v[u].z, c + 2 < V);
-      f(c + 3, v[u].w, c + 3 < V);
+        for (int e = 0; e < 4; ++e) {
+          const float l = at4(v, e);
+          const bool cand = e < n && (!FILT || order_key(l) >= kmin);
+          const float w40 = cand ? f_weight(l, mx, inv_t) : 0.f;
+          acc += f(c + e, w40, (uint64_t)w40);
+        }
+      },
+      [&](int batch) {
+        if constexpr (PIECES) {
+          acc = wave_scan(acc);
+          if (lane == 63) S.pm[w * per + batch] = acc;
+          acc = 0;
+        }
+      });
+}
+
+// Piece of element c, for the masses of S.pm.
+__device__ __forceinline__ int sp_piece(int V, int c) {
+  const int chunk = row_chunk(V), per = (chunk + SP_PIECE - 1) / SP_PIECE;
+  return c / chunk * per + c % chunk / SP_PIECE;
+}
+
+// Top-p threshold among n <= SP_SMALL listed weights with `above` mass over
+// all of them: S.sel[0] = the largest whose heavier-or-equal weights reach
+// need, S.sel[2] = that mass.
+__device__ void sp_reach(SampleLds &S, const uint64_t *list, int n, uint64_t above, uint64_t need) {
+  const int tid = threadIdx.x;
+  const uint64_t q = tid < n ? list[tid] : 0;
+  uint64_t mass = above;
+  if (tid < n)
+    for (int j = 0; j < n; ++j) {
+      const uint64_t o = list[j];
+      mass += o >= q ? o : 0;
     }
-  }
+  const bool reach = tid < n && mass >= need;
+  if (tid == 0) S.sel[0] = 0;
+  __syncthreads();
+  if (reach) atomicMax((unsigned long long *)&S.sel[0], (unsigned long long)q);
+  __syncthreads();
+  if (reach && q == S.sel[0]) S.sel[2] = mass;
+  __syncthreads();
 }
 
 __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ logits, int64_t ld, int V,
                                                        const SampleParams *__restrict__ prm, const int32_t *out_slot,
                                                        int32_t *slot_tok, int32_t *tok_out) {
   __shared__ SampleLds S;
-  const int m = blockIdx.x, tid = threadIdx.x;
-  const float *row = logits + (int64_t)m * ld;
-  const bool vec = (ld % 4 == 0) && (((uintptr_t)logits & 15) == 0);
+  const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const RowPart R = row_part(logits, ld, m, V);
   const SampleParams P = prm[m];
   const bool sampled = P.temperature > 0.f && P.top_p > 0.f && V > 1;
   const bool topk = sampled && P.top_k > 0 && P.top_k < V;
-  // 1. maximum (and the greedy answer), with the top-k first-level counts
-  if (topk) sp_clear(S, SP_NB);
-  __syncthreads();
-  float best = -INFINITY;
-  int bi = 0x7fffffff;
-  sp_row(row, V, vec, [&](int c, float l, bool ok) {
-    if (ok) {
-      argmax_merge(best, bi, l, c);
-      if (topk) atomicAdd((unsigned long long *)&S.hist[order_key(l) >> 21], 1ull);
-    }
-  });
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) argmax_merge(best, bi, __shfl_xor(best, o, 64), __shfl_xor(bi, o, 64));
-  if ((tid & 63) == 0) {
-    S.fmax[tid >> 6] = best;
-    S.imax[tid >> 6] = bi;
-  }
-  __syncthreads();
-  for (int w = 0; w < 16; ++w) argmax_merge(best, bi, S.fmax[w], S.imax[w]);
-  int token = bi;
+  // 1. the maximum
+  const RowBest best = row_best(R);
+  const float mx = row_max(best, S.fmax);
+  int token = -1;  // none yet: the lowest index among the maxima
   if (sampled) {
-    const float mx = best, inv_t = 1.f / P.temperature;
+    const float inv_t = 1.f / P.temperature;
     uint32_t kmin = 0;
     bool in_lds = false;  // candidates (key >= kmin) listed in cq / ci
     if (topk) {
-      // 2. top-k threshold: the top_k-th largest order key, in 11 + 11 + 10 bits
-      sp_select(S, SP_NB, (uint64_t)P.top_k, 0);
-      const uint32_t b0 = (uint32_t)S.sel[1];
-      uint64_t above = S.sel[0];
-      const uint64_t n_hi = S.sel[2];  // elements in bins >= b0
-      __syncthreads();
+      // 2. top-k threshold: the top_k-th largest order key
+      const uint64_t k = (uint64_t)P.top_k;
+      bool listed = false;
+      int lev0 = 0;          // first radix level over the list
+      uint32_t prefix = 0;   // the threshold's bits above that level
+      uint64_t above = 0;    // elements above the prefix
       if (tid == 0) S.n_list = 0;
-      __syncthreads();
-      const bool listed = n_hi <= SP_CAP;
-      if (listed) {
-        sp_row(row, V, vec, [&](int c, float l, bool ok) {
-          const uint32_t k = order_key(l);
-          const int slot = sp_append(ok && (k >> 21) >= b0, &S.n_list);
-          if (slot >= 0 && slot < SP_CAP) {
-            S.lv[slot] = k;
-            S.li[slot] = c;
-          }
-        });
+      if (!__syncthreads_or(best.nan) && P.top_k <= SP_FASTK) {
+        // L: bins of the lanes' maxima, spread over their own range (the bin
+        // of a key is monotone in it), hold at least top_k from L's bin up
+        const uint32_t kb = order_key(best.v);
+        const uint32_t klo = sp_min(kb, S.kred), khi = order_key(mx);
+        const float scale = (float)SP_NB / ((float)(khi - klo) + 1.f);
+        const int bin = min(SP_NB - 1, (int)((float)(kb - klo) * scale));
+        sp_clear(S, SP_NB);
         __syncthreads();
-      }
-      const int n = S.n_list;
-      uint32_t prefix = b0 << 21;
-      for (int level = 1; level < 3; ++level) {
-        const int sh = level == 1 ? 10 : 0, nb = level == 1 ? SP_NB : 1024;
-        const uint32_t pmask = level == 1 ? 0xFFE00000u : 0xFFFFFC00u;
-        sp_clear(S, nb);
+        atomicAdd((unsigned long long *)&S.hist[bin], 1ull);
         __syncthreads();
-        if (listed) {
-          for (int j = tid; j < n; j += SP_T) {
-            const uint32_t k = (uint32_t)S.lv[j];
-            if ((k & pmask) == prefix) atomicAdd((unsigned long long *)&S.hist[(k >> sh) & (nb - 1)], 1ull);
-          }
-        } else {
-          sp_row(row, V, vec, [&](int, float l, bool ok) {
-            const uint32_t k = order_key(l);
-            if (ok && (k & pmask) == prefix) atomicAdd((unsigned long long *)&S.hist[(k >> sh) & (nb - 1)], 1ull);
-          });
+        sp_select(S, SP_NB, k, 0);
+        const uint32_t kl = sp_min(bin >= (int)S.sel[1] ? kb : 0xFFFFFFFFu, S.kred);
+        const bool mine = kb >= kl;
+        if (__ballot(mine)) {
+          row_walk(
+              R,
+              [&](int c, const float4 &v, auto n) {
+                // no lane here reaches L in this piece, most often
+                const float m4 = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));
+                if (!__ballot(mine && order_key(m4) >= kl)) return;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const uint32_t key = order_key(at4(v, e));
+                  const int slot = sp_append(mine && e < n && key >= kl, &S.n_list);
+                  if (slot >= 0 && slot < SP_CAP) {
+                    S.lv[slot] = key;
+                    S.li[slot] = c + e;
+                  }
+                }
+              },
+              [](int) {});
         }
         __syncthreads();
-        sp_select(S, nb, (uint64_t)P.top_k, above);
-        above = S.sel[0];
-        prefix |= (uint32_t)S.sel[1] << sh;
+        listed = S.n_list <= SP_CAP;
+      }
+      if (!listed) {
+        // histograms over the row, in 11 + 11 + 10 bits; the first level's bin
+        // and those above it into the list when they fit
+        sp_clear(S, SP_NB);
         __syncthreads();
+        if (tid == 0) S.n_list = 0;
+        sp_row(R, [&](int, float l, bool ok) {
+          if (ok) atomicAdd((unsigned long long *)&S.hist[order_key(l) >> 21], 1ull);
+        });
+        __syncthreads();
+        sp_select(S, SP_NB, k, 0);
+        const uint32_t b0 = (uint32_t)S.sel[1];
+        above = S.sel[0];
+        listed = S.sel[2] <= SP_CAP;  // elements in bins >= b0
+        lev0 = 1;
+        prefix = b0 << 21;
+        __syncthreads();
+        if (listed) {
+          sp_row(R, [&](int c, float l, bool ok) {
+            const uint32_t key = order_key(l);
+            const int slot = sp_append(ok && (key >> 21) >= b0, &S.n_list);
+            if (slot >= 0 && slot < SP_CAP) {
+              S.lv[slot] = key;
+              S.li[slot] = c;
+            }
+          });
+          __syncthreads();
+        }
+      }
+      const int n = S.n_list;
+      if (listed && n <= SP_SMALL) {
+        // the key with fewer than top_k above it and at least top_k from it up
+        if (tid < n) {
+          const uint32_t key = (uint32_t)S.lv[tid];
+          int gt = 0, ge = 0;
+          for (int j = 0; j < n; ++j) {
+            const uint32_t o = (uint32_t)S.lv[j];
+            gt += o > key;
+            ge += o >= key;
+          }
+          if (gt < P.top_k && P.top_k <= ge) S.sel[3] = key;
+        }
+        __syncthreads();
+        prefix = (uint32_t)S.sel[3];
+      } else {
+        for (int level = lev0; level < 3; ++level) {
+          const int sh = level == 0 ? 21 : level == 1 ? 10 : 0, nb = level == 2 ? 1024 : SP_NB;
+          const uint32_t pmask = level == 0 ? 0u : level == 1 ? 0xFFE00000u : 0xFFFFFC00u;
+          sp_clear(S, nb);
+          __syncthreads();
+          if (listed) {
+            for (int j = tid; j < n; j += SP_T) {
+              const uint32_t key = (uint32_t)S.lv[j];
+              if ((key & pmask) == prefix) atomicAdd((unsigned long long *)&S.hist[(key >> sh) & (nb - 1)], 1ull);
+            }
+          } else {
+            sp_row(R, [&](int, float l, bool ok) {
+              const uint32_t key = order_key(l);
+              if (ok && (key & pmask) == prefix)
+                atomicAdd((unsigned long long *)&S.hist[(key >> sh) & (nb - 1)], 1ull);
+            });
+          }
+          __syncthreads();
+          sp_select(S, nb, k, above);
+          above = S.sel[0];
+          prefix |= (uint32_t)S.sel[1] << sh;
+          __syncthreads();
+        }
       }
       kmin = prefix;
       // the candidates, when few, into the draw list
@@ -522,38 +693,70 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
         in_lds = S.n_cand <= SP_DRAW;
       }
     }
-    // 3. candidate weights: their total and the top-p first-level masses
+    // 3. candidate weights: their total, the top-p threshold tmin, the kept
+    // mass zk and, for a draw over the row, the kept mass of every piece
     const uint32_t pfix = P.top_p >= 1.f ? (1u << 24) : max(1u, (uint32_t)(P.top_p * 16777216.0f));
     const bool topp = pfix < (1u << 24);
     const int nc = in_lds ? S.n_cand : 0;
-    uint64_t z = 0;
-    if (topp) sp_clear(S, SP_NB);
-    __syncthreads();
-    // bin 0 (the many light weights) is left out and later set to the
-    // total minus the other bins
-    if (in_lds) {
-      if (tid < nc) {
-        const uint64_t q = S.cq[tid];
-        z = q;
-        if (topp && q) atomicAdd((unsigned long long *)&S.hist[sp_qbin(q)], (unsigned long long)q);
+    uint64_t tmin = 0, zk = 0;
+    if (in_lds && nc <= SP_SMALL) {
+      const uint64_t q = tid < nc ? S.cq[tid] : 0;
+      uint64_t z;
+      sp_scan(q, S.red, z);
+      zk = z;
+      if (topp) {
+        sp_reach(S, S.cq, nc, 0, mul_shift24(z, pfix, true));
+        tmin = S.sel[0];
+        zk = S.sel[2];
+      }
+    } else if (!topp) {
+      if (in_lds) {
+        sp_scan(tid < nc ? S.cq[tid] : 0, S.red, zk);
+      } else {
+        S.pm[tid] = 0;
+        __syncthreads();
+        auto all = [](int, float, uint64_t q) { return q; };
+        if (kmin) sp_weights<true, true>(S, R, V, kmin, mx, inv_t, all);
+        else sp_weights<false, true>(S, R, V, 0, mx, inv_t, all);
+        __syncthreads();
+        sp_scan(S.pm[tid], S.red, zk);
       }
     } else {
-      sp_row(row, V, vec, [&](int, float l, bool ok) {
-        if (ok && order_key(l) >= kmin) {
-          const uint64_t q = q_weight(l, mx, inv_t);
-          z += q;
-          if (topp && q) atomicAdd((unsigned long long *)&S.hist[sp_qbin(q)], (unsigned long long)q);
+      uint64_t z = 0;
+      sp_clear(S, SP_NB);
+      __syncthreads();
+      // bin 0 is left out and later set to the total minus the other bins
+      if (in_lds) {
+        if (tid < nc) {
+          z = S.cq[tid];
+          if (z) atomicAdd((unsigned long long *)&S.hist[sp_qbin(z)], (unsigned long long)z);
         }
-      });
-    }
-    uint64_t ztot;
-    sp_scan(z, S.red, ztot);
-    z = ztot;
-    if (topp) sp_fill_bin0(S, SP_NB, z);
-    // 4. top-p threshold on weights: a log-scale first level, then the free
-    // low bits of the chosen bin, ten at a time
-    uint64_t tmin = 0, zk = z;
-    if (topp) {
+      } else {
+        // The threshold cannot lie below a weight Q0 with V Q0 <= Z - need (what
+        // is lighter then weighs less than what need leaves out), and Z is at
+        // least the sum over the lanes' maxima: bins below Q0's are not
+        // counted, which spares most rows half of the atomics.
+        uint64_t zlow;
+        sp_scan(order_key(best.v) >= kmin ? q_weight(best.v, mx, inv_t) : 0, S.red, zlow);
+        const uint64_t spare = mul_shift24(zlow, (1u << 24) - pfix, false);
+        uint64_t q0;
+        int q0_bits;
+        sp_qbin_range(sp_qbin(spare > 2 ? (spare - 2) / (uint32_t)V : 0), q0, q0_bits);
+        const float q0f = fmaxf(1.f, (float)q0);  // six significant bits: exact
+        auto bins = [&](int, float w40, uint64_t q) {
+          if (w40 >= q0f) atomicAdd((unsigned long long *)&S.hist[sp_fbin(w40)], (unsigned long long)q);
+          z += q;
+          return (uint64_t)0;
+        };
+        if (kmin) sp_weights<true, false>(S, R, V, kmin, mx, inv_t, bins);
+        else sp_weights<false, false>(S, R, V, 0, mx, inv_t, bins);
+      }
+      uint64_t ztot;
+      sp_scan(z, S.red, ztot);
+      z = ztot;
+      sp_fill_bin0(S, SP_NB, z);
+      // a log-scale first level, then the free low bits of the chosen bin, ten
+      // at a time
       const uint64_t need = mul_shift24(z, pfix, true);
       sp_select(S, SP_NB, need, 0);
       const int b0 = (int)S.sel[1];
@@ -565,27 +768,34 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
       sp_qbin_range(b0, prefix, rem);
       bool listed = in_lds;
       int n = nc;
-      if (!in_lds && rem > 0) {
-        // the weights of bin b0, which the remaining levels refine, when few,
-        // into the list
+      if (!in_lds) {
+        // weights above the bin are kept, and those of the bin, which the
+        // remaining levels refine, listed (a bin of one weight is kept whole)
+        const uint64_t lo = prefix, hi = rem > 0 ? prefix + (1ull << rem) : prefix;
         if (tid == 0) S.n_list = 0;
+        S.pm[tid] = 0;
         __syncthreads();
-        sp_row(row, V, vec, [&](int c, float l, bool ok) {
-          bool keep = ok && order_key(l) >= kmin;
-          uint64_t q = 0;
-          if (keep) {
-            q = q_weight(l, mx, inv_t);
-            keep = q && sp_qbin(q) == b0;
-          }
-          const int slot = sp_append(keep, &S.n_list);
+        // compared before the floor: lo and hi are whole, of six bits
+        const float lof = fmaxf(1.f, (float)lo), hif = (float)hi;
+        auto split = [&](int c, float w40, uint64_t q) {
+          const int slot = sp_append(w40 >= lof && w40 < hif, &S.n_list);
           if (slot >= 0 && slot < SP_CAP) {
             S.lv[slot] = q;
             S.li[slot] = c;
           }
-        });
+          return w40 >= hif ? q : 0;
+        };
+        if (kmin) sp_weights<true, true>(S, R, V, kmin, mx, inv_t, split);
+        else sp_weights<false, true>(S, R, V, 0, mx, inv_t, split);
         __syncthreads();
         n = S.n_list;
         listed = n <= SP_CAP;
+      }
+      if (!in_lds && listed && rem > 0 && n <= SP_SMALL) {
+        sp_reach(S, S.lv, n, above, need);
+        prefix = S.sel[0];
+        zk = S.sel[2];
+        rem = 0;
       }
       while (rem > 0) {
         const int take = min(10, rem), sh = rem - take, nb = 1 << take;
@@ -593,25 +803,18 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
         const uint64_t bucket = zk - above;  // mass of the bin being refined
         sp_clear(S, nb);
         __syncthreads();
+        auto refine = [&](uint64_t q) {
+          if ((q & pmask) == prefix && ((q >> sh) & (nb - 1)))
+            atomicAdd((unsigned long long *)&S.hist[(q >> sh) & (nb - 1)], (unsigned long long)q);
+        };
         if (in_lds) {
-          if (tid < nc) {
-            const uint64_t q = S.cq[tid];
-            if ((q & pmask) == prefix && ((q >> sh) & (nb - 1)))
-              atomicAdd((unsigned long long *)&S.hist[(q >> sh) & (nb - 1)], (unsigned long long)q);
-          }
+          if (tid < nc) refine(S.cq[tid]);
         } else if (listed) {
-          for (int j = tid; j < n; j += SP_T) {
-            const uint64_t q = S.lv[j];
-            if ((q & pmask) == prefix && ((q >> sh) & (nb - 1)))
-              atomicAdd((unsigned long long *)&S.hist[(q >> sh) & (nb - 1)], (unsigned long long)q);
-          }
+          for (int j = tid; j < n; j += SP_T) refine(S.lv[j]);
         } else {
-          sp_row(row, V, vec, [&](int, float l, bool ok) {
-            if (ok && order_key(l) >= kmin) {
-              const uint64_t q = q_weight(l, mx, inv_t);
-              if ((q & pmask) == prefix && ((q >> sh) & (nb - 1)))
-                atomicAdd((unsigned long long *)&S.hist[(q >> sh) & (nb - 1)], (unsigned long long)q);
-            }
+          sp_weights<true, false>(S, R, V, kmin, mx, inv_t, [&](int, float, uint64_t q) {
+            if (q) refine(q);
+            return (uint64_t)0;
           });
         }
         __syncthreads();
@@ -624,22 +827,32 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
         __syncthreads();
       }
       tmin = prefix;
+      if (!in_lds) {
+        if (listed) {  // the listed weights that are kept join their pieces
+          for (int j = tid; j < n; j += SP_T)
+            if (S.lv[j] >= tmin)
+              atomicAdd((unsigned long long *)&S.pm[sp_piece(V, S.li[j])], (unsigned long long)S.lv[j]);
+        } else {
+          sp_weights<true, true>(S, R, V, kmin, mx, inv_t,
+                                 [&](int, float, uint64_t q) { return q >= tmin ? q : (uint64_t)0; });
+        }
+        __syncthreads();
+      }
     }
-    // 5. draw: r in [0, zk), the kept candidate (q >= tmin) whose cumulative
+    // 4. draw: r in [0, zk), the kept candidate (q >= tmin) whose cumulative
     // interval in vocabulary order holds r
     uint32_t c4[4] = {P.counter[0], P.counter[1], P.counter[2], 0x53414D50u};
     philox4x32_10(c4, P.key[0], P.key[1]);
     const uint64_t r = mul_shift24(zk, c4[0] >> 8, false);
-    if (tid == 0) S.found = bi;
+    if (tid == 0) S.found = -1;
     __syncthreads();
     if (in_lds) {
-      const int nk = S.n_cand;
-      if (tid < nk) {
+      if (tid < nc) {
         const uint64_t q = S.cq[tid];
         const int i = S.ci[tid];
         if (q >= tmin) {
           uint64_t pre = 0;
-          for (int j = 0; j < nk; ++j) {
+          for (int j = 0; j < nc; ++j) {
             const uint64_t qj = S.cq[j];
             if (qj >= tmin && S.ci[j] < i) pre += qj;
           }
@@ -647,68 +860,28 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
         }
       }
     } else {
-      // kept mass of every (step, wave) piece of the row: 256 consecutive
-      // elements, in vocabulary order; then the piece that holds r, then the
-      // lane, then the element
-      const int lane = tid & 63, w = tid >> 6;
-      const int steps = (V + 4 * SP_T - 1) / (4 * SP_T), np = steps * 16;
-      for (int s0 = 0; s0 < steps; s0 += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = sp_load4(row, ((s0 + u) * SP_T + tid) * 4, V, vec);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int c = ((s0 + u) * SP_T + tid) * 4;
-          const float lv4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-          uint64_t loc = 0;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (c + e < V && order_key(lv4[e]) >= kmin) {
-              const uint64_t q = q_weight(lv4[e], mx, inv_t);
-              if (q >= tmin) loc += q;
-            }
-          }
-#pragma unroll
-          for (int o = 32; o > 0; o >>= 1) loc += __shfl_xor(loc, o, 64);
-          if (lane == 0 && s0 + u < steps) S.lv[(s0 + u) * 16 + w] = loc;
-        }
-      }
-      __syncthreads();
-      // pieces are scanned in runs of per = ceil(np / SP_T) per thread
-      const int per = (np + SP_T - 1) / SP_T;
-      uint64_t run = 0;
-      for (int i = 0; i < per; ++i) {
-        const int p = tid * per + i;
-        if (p < np) run += S.lv[p];
-      }
+      // the piece that holds r, then the element in it: four a thread
+      const uint64_t run = S.pm[tid];
       uint64_t tot;
-      const uint64_t incl = sp_scan(run, S.red, tot);
-      uint64_t pre = incl - run;
+      uint64_t pre = sp_scan(run, S.red, tot) - run;
       if (tid == 0) S.pick = -1;
       __syncthreads();
       if (run > 0 && r >= pre && r < pre + run) {
-        for (int i = 0; i < per; ++i) {
-          const int p = tid * per + i;
-          if (p >= np) break;
-          const uint64_t q = S.lv[p];
-          if (r < pre + q) {
-            S.pick = p;
-            S.sel[3] = pre;
-            break;
-          }
-          pre += q;
-        }
+        S.pick = tid;
+        S.sel[3] = pre;
       }
       __syncthreads();
       const int p = S.pick;
-      if (p >= 0 && w == p % 16) {
-        const int c = ((p / 16) * SP_T + tid) * 4;
+      if (p >= 0) {
+        const int chunk = row_chunk(V), per = (chunk + SP_PIECE - 1) / SP_PIECE;
+        const int end = min(V, (p / per + 1) * chunk);
+        const int c = p / per * chunk + p % per * SP_PIECE + tid * 4;
         uint64_t q4[4], loc = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           q4[e] = 0;
-          if (c + e < V) {
-            const float l = row[c + e];
+          if (tid < SP_PIECE / 4 && c + e < end) {
+            const float l = R.row[c + e];
             if (order_key(l) >= kmin) {
               const uint64_t q = q_weight(l, mx, inv_t);
               if (q >= tmin) q4[e] = q;
@@ -716,20 +889,11 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
           }
           loc += q4[e];
         }
-        uint64_t x = loc;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const uint64_t t = __shfl_up(x, o, 64);
-          if (lane >= o) x += t;
-        }
-        uint64_t pl = S.sel[3] + x - loc;
+        uint64_t pl = S.sel[3] + sp_scan(loc, S.red, tot) - loc;
         if (loc > 0 && r >= pl && r < pl + loc) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            if (q4[e] && r < pl + q4[e]) {
-              S.found = c + e;
-              break;
-            }
+            if (q4[e] && r >= pl && r < pl + q4[e]) S.found = c + e;
             pl += q4[e];
           }
         }
@@ -738,6 +902,7 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
     __syncthreads();
     token = S.found;
   }
+  if (token < 0) token = row_first(R, best, mx, S.imax);
   if (tid == 0) {
     if (out_slot) slot_tok[out_slot[m]] = token;
     tok_out[m] = token;
@@ -747,7 +912,7 @@ __global__ __launch_bounds__(SP_T) void sample_kernel(const float *__restrict__ 
 void launch_sample(const float *logits, int64_t ld, int M, int V, const SampleParams *prm, const int32_t *out_slot,
                    int32_t *slot_tok, int32_t *tok_out, hipStream_t s) {
   if (M <= 0) return;
-  sample_kernel<<<M, 1024, 0, s>>>(logits, ld, V, prm, out_slot, slot_tok, tok_out);
+  sample_kernel<<<M, SP_T, 0, s>>>(logits, ld, V, prm, out_slot, slot_tok, tok_out);
 }
 
 template <typename T>

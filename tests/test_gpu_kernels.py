@@ -325,6 +325,31 @@ def test_argmax_strides_and_tails(V, ld):
     assert out.cpu().numpy().tolist() == [int(np.argmax(r[:V])) for r in full]
 
 
+@pytest.mark.parametrize("V,shift", [(3, 0), (256, 0), (5000, 0), (5000, 1), (70000, 0)])
+def test_argmax_special_values(V, shift):
+    """NaN is never chosen, -inf only where nothing is larger, zeros of either
+    sign tie; rows on and off 16 bytes, shorter than a step and several long."""
+    rng = np.random.default_rng(V)
+    rows = [(rng.standard_normal(V) * 2).astype(np.float32) for _ in range(6)]
+    rows[0][::2] = np.nan
+    rows[1][:] = -np.inf
+    rows[1][: V // 2] = np.nan
+    rows[2][:] = np.nan
+    rows[3][:] = -np.inf
+    rows[3][V - 1] = np.finfo(np.float32).min
+    rows[4] = -np.abs(rows[4])
+    rows[4][[V // 3, V - 1]] = [-0.0, 0.0]
+    rows[5][[V // 2, V - 1]] = np.inf
+    buf = torch.zeros(6 * V + 4, dtype=torch.float32, device=DEV)
+    L = buf[shift:shift + 6 * V].view(6, V)
+    L.copy_(torch.from_numpy(np.stack(rows)))
+    out = torch.empty(6, dtype=torch.int32, device=DEV)
+    lp.op_argmax(L, out)
+    torch.cuda.synchronize()
+    want = [int(np.nanargmax(rows[0])), V // 2, 0x7FFFFFFF, V - 1, V // 3, V // 2]
+    assert out.cpu().numpy().tolist() == want
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_device_weight_generator_matches_host(dtype):
     rows, cols, tid, seed = 300, 688, 17, 0x1234ABCD5678

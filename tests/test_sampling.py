@@ -140,6 +140,63 @@ def test_sample_kernel_matches_oracle(V):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("V,pad,shift", [(2, 0, 0), (5, 3, 0), (255, 0, 0), (2048, 0, 0), (4097, 1, 0), (33000, 0, 1)])
+def test_sample_kernel_edges(V, pad, shift):
+    """Both sides of the kernel's rules: top_k at and past the lanes' selection
+    (512), candidate sets either side of 256 and of the LDS draw's 1,024, bins
+    with few and many weights, masked rows (-inf and the type's lowest value),
+    ties, rows off 16 bytes and short of one step, lanes without elements."""
+    import torch
+    rng = np.random.default_rng(V)
+    combos = [(0.0, 0, 1.0), (1.0, 0, 1.0), (1.0, 1, 1.0), (0.7, 40, 0.9), (1.0, 200, 0.99), (0.9, 300, 0.95),
+              (1.2, 512, 1.0), (1.2, 513, 0.8), (1.0, 1500, 0.9), (1.0, 0, 0.9), (1.0, 0, 0.3), (3.0, 0, 0.97)]
+    rows, logits = [], []
+    for i, (t, k, p) in enumerate(combos * 3):
+        l = (rng.standard_normal(V) * (0.5, 2.0, 8.0)[i % 3]).astype(np.float32)
+        kind = i // len(combos)
+        if kind == 1:
+            low = -np.inf if i % 2 else np.finfo(np.float32).min
+            l[rng.random(V) < 0.7] = low                # masked vocabulary
+            l[rng.integers(0, V)] = 1.0
+        if kind == 2:
+            l = np.round(l * 2).astype(np.float32) / 2  # ties everywhere
+        logits.append(l)
+        rows.append((t, k, p, (int(rng.integers(0, 2**32)), int(rng.integers(0, 2**32))), (i, 0, 7)))
+    n, ld = len(rows), V + pad
+    buf = torch.full((n * ld + 8,), 1e30, dtype=torch.float32, device="cuda")
+    L = buf[shift:shift + n * ld].view(n, ld)[:, :V]
+    L.copy_(torch.tensor(np.stack(logits)))
+    prm = torch.tensor(lp.sample_params_array(rows), device="cuda")
+    tok = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    lp.op_sample(L, prm, tok)
+    torch.cuda.synchronize()
+    got = tok.cpu().numpy()
+    kinds = [check(logits[i].astype(np.float64), t, k, p, SP.draw_u24(key, ctr), int(got[i]))
+             for i, (t, k, p, key, ctr) in enumerate(rows)]
+    assert kinds.count("exact") >= len(kinds) - 1
+
+
+@pytest.mark.gpu
+def test_sample_kernel_nan_rows_take_the_histogram_selection():
+    """A NaN is no maximum, weighs 0 and is never drawn; rows that hold one
+    select their top_k on histograms, where it counts as a largest value: a
+    row whose top_k leaves NaN only falls back to its maximum."""
+    import torch
+    rng = np.random.default_rng(3)
+    l = (rng.standard_normal((3, 9000)) * 2).astype(np.float32)
+    l[:, 17] = np.nan
+    prm = [(1.0, 40, 1.0, (1, 2), (0, 0, 0)), (1.0, 1, 1.0, (3, 4), (1, 0, 0)), (0.0, 0, 1.0, (5, 6), (2, 0, 0))]
+    tok = torch.full((3,), -1, dtype=torch.int32, device="cuda")
+    lp.op_sample(torch.tensor(l, device="cuda"), torch.tensor(lp.sample_params_array(prm), device="cuda"), tok)
+    torch.cuda.synchronize()
+    got = tok.cpu().numpy()
+    # top_k 40 keeps the NaN and the 39 largest numbers
+    clean = np.where(np.isnan(l[0]), -np.inf, l[0]).astype(np.float64)
+    assert check(clean, 1.0, 39, 1.0, SP.draw_u24(prm[0][3], prm[0][4]), int(got[0])) == "exact"
+    assert got[1] == np.nanargmax(l[1]) and got[2] == np.nanargmax(l[2])
+
+
+@pytest.mark.gpu
 def test_engine_draws_with_each_requests_parameters():
     """Every token the engine emits is the sampler's choice on the logits that
     produced it, with the request's parameters and the draw keyed by (seed,
