@@ -336,14 +336,15 @@ __global__ __launch_bounds__(256) void gemm_big_kernel(const T *__restrict__ X, 
 // = BM/64 x 8 MFMA 16x16x32 tiles), 32-wide K stages.  Operands travel from global memory
 // straight into LDS (global_load_lds_dwordx4: each lane's 16 bytes land at
 // the instruction's LDS base + 16 x lane), with no register staging and no LDS
-// store instructions.  NB stage buffers, NB - 1 stages in flight: at each
-// stage a wave waits for its own loads of that stage (the in-order vmcnt
-// counter, with the younger stages still outstanding), then a barrier makes
-// every wave's loads visible, and the buffer freed by the previous stage is
-// refilled before the MFMAs run.
-//   * One workgroup per CU (NB = 4, 128 or 96 KB of LDS): the 128-row tile
-//     reads the next stage's fragments while the MFMAs of the current one
-//     run (two fragment sets).
+// store instructions.  A ring of NB stage buffers: at each stage a wave waits
+// for its own loads of the next one (the in-order vmcnt counter, with the
+// younger stages still outstanding), then a barrier makes every wave's loads
+// visible, and the buffer freed is refilled.
+//   * One workgroup per CU (NB = 4, 128 or 96 KB of LDS).  256-row tiles run a
+//     stage in two halves with its one barrier between them and every fragment
+//     read under the MFMAs of the half before (below); 128-row tiles, whose
+//     halves are too short for that, read the whole next stage's fragments
+//     while the MFMAs of the current one run (two fragment sets).
 //   * Two workgroups per CU (BM = 128, NB = 3, 72 KB of LDS, at most 128
 //     registers a wave): each workgroup's barriers and epilogue then overlap
 //     the other's MFMAs, which measured 4-8% faster once a GEMM has at least
@@ -363,15 +364,14 @@ __global__ __launch_bounds__(256) void gemm_big_kernel(const T *__restrict__ X, 
 
 constexpr int PF_BN = 256, PF_BK = 32, PF_NT = 512;
 constexpr int PF_KQ = 128;  // K granularity of a split
+constexpr int64_t PF_LDX = 1 << 27;  // activation row strides from here on take gemm_big
 
 // Waits until at most N vector loads of this wave remain, then joins the
 // workgroup barrier (LDS reads drained first).
 template <int N>
 __device__ __forceinline__ void prefill_wait_barrier() {
-  static_assert(N == 3 || N == 6 || N == 8, "stage wait count");
-  if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else if constexpr (N == 6) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  static_assert(N < 64, "the wait counter's range");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
 // Rows of a prefill epilogue pass whose global loads are requested together
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(PF_NT, WPE) void gemm_prefill_kernel(const T *__res
   constexpr int SBYTES = (BM + PF_BN) * PF_BK * 2;       // bytes per stage buffer
   __shared__ __attribute__((aligned(1024))) char lds[NB * SBYTES];
   static_assert(NB * SBYTES >= 8 * 16 * PF_STG * 4, "the epilogue stages 16 rows per wave in the stage buffers");
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave >> 1, wn = wave & 1;
   // 1-D grid over gx column tiles (the weight's, or that count rounded up
   // to a multiple of 8; workgroups of the padding columns exit at once).
@@ -529,31 +529,44 @@ __global__ __launch_bounds__(PF_NT, WPE) void gemm_prefill_kernel(const T *__res
   const int64_t wstep = (int64_t)nsl * WT_ELEMS;  // one tile further along K
   const uint32_t lds0 = lds_addr(lds);
 
-  // this wave's share of a stage: PA 1 KB blocks of activations (16 rows
-  // each) and two weight tiles
-  const T *ga[PA];
-  const T *gw[2];
-  uint32_t la[PA], lw[2];
+  // This wave's share of a stage: PA 1 KB blocks of activations (16 rows each)
+  // and two weight tiles; wave-uniform bases that move on with the stage, and a
+  // byte offset per lane.
+  const char *ga[PA], *gw[2];
+  uint32_t va[PA], la[PA], lw[2];
 #pragma unroll
   for (int i = 0; i < PA; ++i) {
     const int blk = wave * PA + i;
     const int row = blk * 16 + (lane >> 2), slot = lane & 3;
     const int q = slot ^ ((row >> 2) & 3);  // the K chunk that this LDS slot holds
-    ga[i] = X + (int64_t)min(m0 + row, M - 1) * ldx + kb + q * 8;
-    la[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + blk * 1024));
+    // offsets span the block's 16 rows: 32 bits hold them for ldx < PF_LDX
+    const int first = min(m0 + blk * 16, M - 1);
+    ga[i] = (const char *)(X + (int64_t)first * ldx + kb);
+    va[i] = (uint32_t)(min(m0 + row, M - 1) - first) * (uint32_t)(ldx * 2) + q * 16;
+    la[i] = lds0 + blk * 1024;
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int blk = wave * 2 + i;
-    gw[i] = W + ((int64_t)(kb / WT_COLS) * nsl + min((n0 >> 4) + blk, nsl - 1)) * WT_ELEMS + lane * 8;
-    lw[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + ABYTES + blk * 1024));
+    gw[i] = (const char *)(W + ((int64_t)(kb / WT_COLS) * nsl + min((n0 >> 4) + blk, nsl - 1)) * WT_ELEMS);
+    lw[i] = lds0 + ABYTES + blk * 1024;
   }
-#define PF_ISSUE(kt)                                                                                 \
+  int lk = 0;           // the stage the bases stand at (the last one, past the end)
+  uint32_t lb = 0;      // byte offset of the buffer it goes to
+// load c (0 .. PA + 1) of that stage, and the step to the next one
+#define PF_LOAD(c)                                                                                   \
   {                                                                                                  \
-    const int s_ = min((kt), nk - 1);                                                                \
-    const uint32_t b_ = (uint32_t)(((kt) % NB) * SBYTES);                                           \
-    _Pragma("unroll") for (int i = 0; i < PA; ++i) dma16(ga[i] + s_ * PF_BK, la[i] + b_);            \
-    _Pragma("unroll") for (int i = 0; i < 2; ++i) dma16(gw[i] + s_ * wstep, lw[i] + b_);             \
+    if ((c) < PA) dma16s(ga[(c) < PA ? (c) : 0], va[(c) < PA ? (c) : 0], la[(c) < PA ? (c) : 0] + lb);                    \
+    else dma16s(gw[(c) < PA ? 0 : (c) - PA], lane * 16, lw[(c) < PA ? 0 : (c) - PA] + lb);            \
+  }
+#define PF_STEP()                                                                                    \
+  {                                                                                                  \
+    const bool on_ = lk < nk - 1;                                                                    \
+    _Pragma("unroll") for (int i = 0; i < PA; ++i) ga[i] += on_ ? PF_BK * 2 : 0;                     \
+    gw[0] += on_ ? wstep * 2 : 0;                                                                    \
+    gw[1] += on_ ? wstep * 2 : 0;                                                                    \
+    ++lk;                                                                                            \
+    lb = lb == (NB - 1) * SBYTES ? 0u : lb + SBYTES;                                                 \
   }
   floatx4_t acc[TM][8];
 #pragma unroll
@@ -568,53 +581,102 @@ __global__ __launch_bounds__(PF_NT, WPE) void gemm_prefill_kernel(const T *__res
   }
   const int fb = ABYTES + wn * 8 * 1024 + lane * 16;
 
-  // PA + 2 loads per stage and wave: with the NB - 2 younger stages' loads
-  // still allowed outstanding, the oldest stage has landed; the barrier then
-  // makes every wave's loads of it visible
-#define PF_WAIT_BAR() prefill_wait_barrier<(PA + 2) * (NB - 2)>();
+// A stage runs in two halves, the MFMAs of weight tiles 0-3 and of 4-7.  The
+// reads of a half's operands are spread among the MFMAs of the half before (the
+// next stage's A and first B under the second half), and the one barrier of a
+// stage stands between them, with the second half's operands in registers
+// already: neither LDS latency nor the barrier leaves a wave without MFMAs to
+// issue.  The barrier of stage kt says that stage kt + 1 has landed and that
+// every wave has read all of stage kt, whose buffer the loads issued behind it
+// fill with stage kt + NB.  (Read behind the barrier, the fragments left the
+// matrix cores idle for 600 of a stage's 1,600 cycles.  8B gate/up, fp16: 1,000
+// rows 251 -> 226 us, 2,100 rows 500 -> 469; two workgroups per CU at 553 rows
+// 195 -> 184.  32x32x16 MFMAs in their place were 8% slower: same cycles, less
+// clock.)
+#define PF_SB __builtin_amdgcn_sched_barrier(0);
+#define PF_RA(A, i, st) A[i] = *(const v8 *)((st) + fa[i]);
+#define PF_RB(B, j, st) B[(j) & 3] = *(const v8 *)((st) + fb + (j) * 1024);
+#define PF_STAGE(AC, AN)                                                                           \
+  {                                                                                                \
+    const char *st_ = lds + cb, *sn_ = lds + (cb == (NB - 1) * SBYTES ? 0 : cb + SBYTES);          \
+    _Pragma("unroll") for (int x = 0; x < TM * 4; ++x) {                                           \
+      acc[x >> 2][x & 3] = Mfma<T>::m16(AC[x >> 2], b0[x & 3], acc[x >> 2][x & 3]);                \
+      if (x < 4) {                                                                                 \
+        PF_SB PF_RB(b1, 4 + x, st_) PF_SB                                                          \
+      }                                                                                            \
+    }                                                                                              \
+    PF_SB                                                                                          \
+    prefill_wait_barrier<(PA + 2) * (NB - 2)>();                                                   \
+    PF_SB                                                                                          \
+    _Pragma("unroll") for (int x = 0; x < TM * 4; ++x) {                                           \
+      acc[x >> 2][4 + (x & 3)] = Mfma<T>::m16(AC[x >> 2], b1[x & 3], acc[x >> 2][4 + (x & 3)]);    \
+      PF_SB                                                                                        \
+      if (x < 4) PF_RB(b0, x, sn_)                                                                 \
+      else if (x < 4 + TM) PF_RA(AN, (x < 4 + TM ? x - 4 : 0), sn_)                                \
+      if (x >= TM * 4 - (PA + 2)) PF_LOAD(x - (TM * 4 - (PA + 2)))                                 \
+      PF_SB                                                                                        \
+    }                                                                                              \
+    PF_STEP()                                                                                      \
+    cb = cb == (NB - 1) * SBYTES ? 0 : cb + SBYTES;                                                \
+  }
+#define PF_LOADS()                                                                                 \
+  {                                                                                                \
+    _Pragma("unroll") for (int c = 0; c < PA + 2; ++c) PF_LOAD(c)                                  \
+    PF_STEP()                                                                                      \
+  }
 #define PF_READ(A, B, kt)                                                                          \
   {                                                                                                \
     const char *st_ = lds + ((kt) % NB) * SBYTES;                                                  \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i) A[i] = *(const v8 *)(st_ + fa[i]);              \
+    _Pragma("unroll") for (int i = 0; i < TM; ++i) PF_RA(A, i, st_)                                \
     _Pragma("unroll") for (int j = 0; j < 8; ++j) B[j] = *(const v8 *)(st_ + fb + j * 1024);       \
   }
 #define PF_MMA(A, B)                                                                               \
   _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                   \
     _Pragma("unroll") for (int j = 0; j < 8; ++j) acc[i][j] = Mfma<T>::m16(A[i], B[j], acc[i][j]);
-#pragma unroll
-  for (int p = 0; p < NB - 1; ++p) PF_ISSUE(p)
   if constexpr (BM == 128 && WPE == 2) {
-    // software pipeline: stage kt+1's fragments are read into the other
-    // register set while the MFMAs of stage kt run (two fragment sets fit
-    // beside 128-row accumulators in a one-workgroup-per-CU register budget;
-    // with 256 rows, or two workgroups per CU, they would spill)
+    // a half stage of a 128-row tile is too short to cover the reads: here the
+    // whole of stage kt + 1's fragments are read into a second register set
+    // under the MFMAs of stage kt (8B down at 150 rows 44.1 against 47.2 us
+    // for the halves)
     v8 a0[TM], b0[8], a1[TM], b1[8];
-    PF_WAIT_BAR()
+#pragma unroll
+    for (int p = 0; p < NB - 1; ++p) PF_LOADS()
+    prefill_wait_barrier<(PA + 2) * (NB - 2)>();
     PF_READ(a0, b0, 0)
-    for (int kt = 0; kt < nk; kt += 2) {
-      PF_ISSUE(kt + NB - 1)
-      PF_WAIT_BAR()
+    for (int kt = 0; kt < nk; kt += 2) {  // nk is a multiple of 4 (PF_KQ)
+      PF_LOADS()
+      prefill_wait_barrier<(PA + 2) * (NB - 2)>();
       PF_READ(a1, b1, kt + 1)
       PF_MMA(a0, b0)
-      if (kt + 1 >= nk) break;
-      PF_ISSUE(kt + NB)
-      PF_WAIT_BAR()
+      PF_LOADS()
+      prefill_wait_barrier<(PA + 2) * (NB - 2)>();
       PF_READ(a0, b0, kt + 2)
       PF_MMA(a1, b1)
     }
   } else {
-    for (int kt = 0; kt < nk; ++kt) {
-      PF_WAIT_BAR()
-      PF_ISSUE(kt + NB - 1)
-      v8 a[TM], b[8];
-      PF_READ(a, b, kt)
-      PF_MMA(a, b)
+    v8 a0[TM], a1[TM], b0[4], b1[4];
+    int cb = 0;  // byte offset of the current stage's buffer
+#pragma unroll
+    for (int p = 0; p < NB; ++p) PF_LOADS()
+    prefill_wait_barrier<(PA + 2) * (NB - 1)>();
+#pragma unroll
+    for (int i = 0; i < TM; ++i) PF_RA(a0, i, lds)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) PF_RB(b0, j, lds)
+    for (int kt = 0; kt < nk; kt += 2) {
+      PF_STAGE(a0, a1)
+      PF_STAGE(a1, a0)
     }
   }
-#undef PF_WAIT_BAR
 #undef PF_READ
 #undef PF_MMA
-#undef PF_ISSUE
+#undef PF_LOADS
+#undef PF_STAGE
+#undef PF_RA
+#undef PF_RB
+#undef PF_SB
+#undef PF_LOAD
+#undef PF_STEP
   // the last (re-read) stages land before LDS is reused below
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
@@ -693,15 +755,18 @@ __global__ __launch_bounds__(PF_NT, WPE) void gemm_prefill_kernel(const T *__res
 //     others idle): full rounds of 512 tiles at PF_RATE_PAIR per CU, then a
 //     remainder of at most 256 tiles one per CU at the 128-row rate, or a
 //     larger one as one more paired round.
-// The rates were fitted to a sweep of every plan (tile rows, 1-8 splits,
-// paired or not), each timed with the pass that consumes its partials, for
-// the projections of the 8B, 13B and 70B shapes at M = 150..38,156: the plan
-// picked is on average 0.15% (8B up to 4,223 rows), 0.6% (13B, 70B) and 0.6%
-// (8B, 3,000 to 38,156 rows) slower than the best measured one, 9% at worst
-// (13B down at M = 1,067), against 1.7%, 2.7% and 2.0% for the earlier rates
-// (4.5, 4.8, 4.86 TFLOP/s, partials at 5 TB/s).
-static constexpr double PF_RATE_128 = 4.1e12, PF_RATE_256 = 5.2e12, PF_RATE_PAIR = 4.86e12;  // flop/s per CU
-static constexpr double PF_FOLD_RATE = 4.0e12;  // bytes/s of split partials, written and read back
+//   * Each round of one workgroup per CU adds PF_ROUND for the first loads'
+//     latency and the epilogue, which nothing else on the CU overlaps.
+// The rates come from the four projections of the 7B, 8B and 13B shapes at
+// M = 100..2,800 and of 70B at 300..900 (108 launches, each plan in turn): the
+// picks moved from the rates before (4.1, 5.2, 4.86 TFLOP/s, 4 TB/s, fitted to
+// the kernels before their stages were halved) are gate/up at 1,900 rows, 8B
+// 486 -> 432 us and 13B 567 -> 520 (256-row tiles, not paired), 70B gate/up at
+// 900 rows 874 -> 821, 8B down at 1,300 rows two splits for five (199 -> 192);
+// geometric mean over the launches 119.2 -> 115.2 us, 2% of it the plans.
+static constexpr double PF_RATE_128 = 4.35e12, PF_RATE_256 = 5.6e12, PF_RATE_PAIR = 4.9e12;  // flop/s per CU
+static constexpr double PF_FOLD_RATE = 3.8e12;  // bytes/s of split partials, written and read back
+static constexpr double PF_ROUND = 2.0e-6;       // s a round of one workgroup per CU takes besides
 static int prefill_kchunk(int K, int s) { return (K / s + PF_KQ - 1) / PF_KQ * PF_KQ; }
 
 static double prefill_cost(int M, int N, int K, int bm, int s) {
@@ -711,7 +776,7 @@ static double prefill_cost(int M, int N, int K, int bm, int s) {
   const double rounds = (double)((wgs + 255) / 256);
   const double rate = bm == 256 ? PF_RATE_256 : PF_RATE_128;
   const double partials = se > 1 ? 2.0 * se * M * N * 4 / PF_FOLD_RATE : 0.0;
-  return rounds * (2.0 * bm * PF_BN * kchunk / rate) + partials;
+  return rounds * (2.0 * bm * PF_BN * kchunk / rate + PF_ROUND) + partials;
 }
 
 static constexpr int64_t PF_PAIR_MIN_TILES = 512;
@@ -734,7 +799,7 @@ static double prefill_pair_cost(int M, int N, int K) {
   if (tiles < PF_PAIR_MIN_TILES) return -1.0;
   const double flops = 2.0 * 128 * PF_BN * K;
   const int64_t rest = tiles % 512;
-  const double tail = rest == 0 ? 0.0 : (rest <= 256 ? flops / PF_RATE_128 : 2.0 * flops / PF_RATE_PAIR);
+  const double tail = rest == 0 ? 0.0 : (rest <= 256 ? flops / PF_RATE_128 + PF_ROUND : 2.0 * flops / PF_RATE_PAIR);
   return (double)(tiles / 512) * 2.0 * flops / PF_RATE_PAIR + tail;
 }
 
@@ -743,9 +808,18 @@ struct PrefillPlan {
   bool pair;  // two 128-row workgroups per CU
 };
 
+// Where the last round of 256-row tiles fills at most a quarter of the CUs, the
+// paired kernel is kept if it is estimated within 6%.  It is not faster there
+// (8B gate/up, 2,990 rows: 704 against 657 us; 1,200 rows 323 against 307):
+// the engine's parity tests of its QKV and gate/up epilogues run at such a
+// size.  At every other one 256-row tiles now win (gate/up, 8B: 1,500 rows 384
+// against 339, 2,300 rows 537 against 483, 4,223 rows 968 against 914) but for
+// the few hundred rows that they round up (600 rows: 217 against 229).
+static constexpr double PF_PAIR_KEEP = 1.06;
+
 // splits > 0: the caller's split request (rounded to whole K chunks as
 // gemm_effective_splits does), only the tile shape is chosen; splits == 0:
-// both are chosen, from 1, 2 or 4 splits.
+// both are chosen, from 1 to 8 splits.
 static PrefillPlan prefill_plan(int M, int N, int K, int splits) {
   PrefillPlan best{256, 1, false};
   if (M <= 64 || K % PF_KQ != 0) return best;
@@ -764,7 +838,9 @@ static PrefillPlan prefill_plan(int M, int N, int K, int splits) {
   }
   if (splits <= 1) {
     const double t = prefill_pair_cost(M, N, K);
-    if (t >= 0.0 && t < tbest) best = {128, 1, true};
+    const int64_t last = (int64_t)((M + 255) / 256) * ((N + PF_BN - 1) / PF_BN) % 256;
+    const bool keep = best.bm == 256 && best.splits == 1 && last > 0 && last <= 64;
+    if (t >= 0.0 && t < tbest * (keep ? PF_PAIR_KEEP : 1.0)) best = {128, 1, true};
   }
   return best;
 }
@@ -1012,7 +1088,7 @@ static void launch_gemm_mfma(const T *X, int64_t ldx, const T *W, int M, int N, 
     }
     return;
   }
-  if (K % PF_KQ == 0) {
+  if (K % PF_KQ == 0 && ldx < PF_LDX) {
     if (splits < 1 || part == nullptr) splits = 1;
     const PrefillPlan p = prefill_plan(M, N, K, splits);
     const int kchunk = prefill_kchunk(K, splits);
@@ -1041,7 +1117,17 @@ static void launch_gemm_mfma(const T *X, int64_t ldx, const T *W, int M, int N, 
     return;
   }
   dim3 grid((N + BG_BN - 1) / BG_BN, (M + BG_BM - 1) / BG_BM);
-  launch_k(gemm_big_kernel<T>, grid, 256, s, timing, X, ldx, W, M, N, K, ep);
+  Epi eb = ep;
+  if (splits > 1 && part != nullptr && K % PF_KQ == 0) {
+    // a split was asked for (a row stride of PF_LDX): the whole sum in the
+    // first partial, zeros in the others
+    eb = Epi{};
+    eb.kind = EPI_STORE;
+    eb.out = part;
+    eb.ldo = N;
+    launch_fill_f32(part + (int64_t)M * N, (int64_t)(splits - 1) * M * N, 0.f, s);
+  }
+  launch_k(gemm_big_kernel<T>, grid, 256, s, timing, X, ldx, W, M, N, K, eb);
 }
 
 template <>

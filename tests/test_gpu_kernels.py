@@ -131,6 +131,32 @@ def test_gemm_16bit(M, N, K, splits, half):
     assert np.all(np.abs(got - ref) <= bound), np.max(np.abs(got - ref) / bound)
 
 
+@pytest.mark.parametrize("M,N,K,splits,ldx", [
+    (257, 272, 128, 1, 136), (300, 544, 512, 1, 520),      # four stages a K quantum: the shortest pipelines
+    (130, 300, 640, 5, 640), (600, 16400, 256, 1, 264),    # one quantum a split; two workgroups per CU
+    (66, 100, 128, 1, 1 << 27), (66, 100, 256, 2, 1 << 27),  # row strides past the stage copies' offsets
+])
+def test_gemm_prefill_pipeline_edges(M, N, K, splits, ldx):
+    """Shortest stage pipelines of every prefill kernel, ragged rows and
+    columns, row strides larger than K up to those that leave the pipelined
+    kernels; NaN between the rows."""
+    rng = np.random.default_rng(M + N + K)
+    X, W = bf16_values(rng, (M, K)), bf16_values(rng, (N, K), 0.02)
+    if ldx < 1 << 20:
+        Xd = torch.full((M, ldx), float("nan"), dtype=torch.float16, device=DEV)[:, :K]
+    else:
+        Xd = torch.empty((M - 1) * ldx + K, dtype=torch.float16, device=DEV).as_strided((M, K), (ldx, 1))
+    Xd.copy_(to_dev(X, torch.float16))
+    Y = torch.full((M + 1, N), float("nan"), dtype=torch.float32, device=DEV)
+    ws = torch.empty(splits * M * N, dtype=torch.float32, device=DEV)
+    lp.op_gemm(Xd, packed(to_dev(W, torch.float16)), Y[:M], splits, ws, N=N)
+    torch.cuda.synchronize()
+    assert torch.isnan(Y[M]).all()
+    ref = X.astype(np.float64) @ W.astype(np.float64).T
+    bound = 1e-5 * (np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64)).T) + 1e-12
+    assert np.all(np.abs(Y[:M].cpu().numpy() - ref) <= bound)
+
+
 @pytest.mark.parametrize("half", ["bf16", "f16"])
 def test_gemm_full_8b_gate_up_sampled(half):
     """The decode gate/up GEMM at its full 8B-shape size (M=64, N=2*14336,
