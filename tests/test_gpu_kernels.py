@@ -559,3 +559,33 @@ def test_zero_row_calls_through_the_binding():
     lp.op_sample(logits, prm, tok[:0])
     torch.cuda.synchronize()
     assert tok.cpu().tolist() == [-7] * 4
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,ulp_bits", [("f16", 10), ("bf16", 7)])
+def test_prefill_attention_largest_weight_is_not_rounded(dtype, ulp_bits):
+    """One key after the first block outweighs the others by 2^1 to 2^8 and is
+    the only one with values: its probability is the row's largest, exactly 1
+    in 16 bits, so the output is the weight rounded once (half a unit in the
+    last place; fp32 sums and exp2 add under 1e-5)."""
+    import torch
+    from paper_2410_02425_amd import lp
+    dt = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    heads, hd, n, at = 32, 128, 130, 70
+    a = (torch.linspace(1.0, 7.9, heads) * np.log(2.0) * np.sqrt(hd) / 4.0).to(dt)
+    q = torch.zeros(n, heads, hd, dtype=dt)
+    q[:, :, 0] = a
+    k = torch.zeros(3, heads, 64, hd, dtype=dt)
+    v = torch.zeros(3, heads, hd, 64, dtype=dt)
+    k[at // 64, :, at % 64, 0] = 4.0
+    v[at // 64, :, :, at % 64] = 1.0
+    out = torch.zeros(n, heads, hd, dtype=dt, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    lp.op_prefill_attention(q.cuda(), out, k.cuda(), v.cuda(), torch.arange(3, **i32).view(1, 3),
+                            torch.tensor([0, n], **i32), torch.zeros(1, **i32), n, heads)
+    got = out.cpu().double()
+    big = torch.exp(a.double() * 4.0 / np.sqrt(hd))[None, :]
+    others = torch.arange(n, dtype=torch.float64)[:, None]
+    want = torch.where(others >= at, big / (big + others), torch.zeros(()).double())
+    half_ulp = torch.exp2(torch.floor(torch.log2(want.clamp_min(1e-30))) - ulp_bits - 1)
+    assert ((got - want[:, :, None]).abs() <= (half_ulp + 1e-5 * want)[:, :, None]).all()
