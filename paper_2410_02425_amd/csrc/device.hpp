@@ -167,20 +167,20 @@ __device__ __forceinline__ float lane_xor1(float v) {
 }
 
 // 16 bytes per lane from global memory straight into LDS (gfx950's
-// global_load_lds_dwordx4): lane l's bytes land at LDS byte address
-// `lds` + 16 l, `lds` wave-uniform.  The load counts on vmcnt like any vector
-// load but is invisible to the compiler's wait-count tracking: callers wait
-// for it explicitly (s_waitcnt vmcnt) before a barrier and reading the data.
-__device__ __forceinline__ void dma16(const void *g, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
-}
-
-// The same from a wave-uniform base and a byte offset per lane.
+// global_load_lds_dwordx4), from a wave-uniform base and a byte offset per
+// lane: lane l's bytes land at LDS byte address `lds` + 16 l, `lds`
+// wave-uniform.  The load counts on vmcnt like any vector load but is invisible
+// to the compiler's wait-count tracking: callers wait for it explicitly
+// (s_waitcnt vmcnt) before a barrier and reading the data.  A load into LDS may
+// not issue right behind the scalar write of M0 that it takes its LDS address
+// from (one wait state, which the compiler inserts for its own loads but not
+// inside an asm block): the s_nop.
 __device__ __forceinline__ void dma16s(const void *base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
 }
 
-// LDS byte address of a __shared__ object (for dma16).
+// LDS byte address of a __shared__ object (for dma16s).
 __device__ __forceinline__ uint32_t lds_addr(const void *p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char *)p;
 }
