@@ -121,7 +121,9 @@ int lp_op_prefill_attention(int32_t dtype, const void *q, void *out, const void 
 
 /* Greedy decoding, the token choice of each prefill and decode step of Sec.
  * II-A under greedy requests: tokens[m] = argmax of logits row m (fp32, row
- * stride ld), lowest index on ties.  tokens [M] int32 (device). */
+ * stride ld), lowest index on ties; a NaN is never chosen, and a row of
+ * nothing but NaN gives 0x7fffffff (which the engine embeds as NaN).
+ * tokens [M] int32 (device). */
 int lp_op_argmax(const float *logits, int64_t ld, int32_t M, int32_t V, int32_t *tokens, void *hip_stream);
 
 /* The device weight generator (see lp_init_weights_random): dst[rows x cols]

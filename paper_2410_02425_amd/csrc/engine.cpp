@@ -905,16 +905,18 @@ static int launch_step(lp_engine *e, const PlanStep &ps, int64_t step, int64_t l
   float *x = e->ptr<float>(e->Ly.x);
   switch (e->D.act) {
     case ACT_F16:
-      launch_embed<f16_t>(e->ptr<f16_t>(e->Ly.embed), pool, dm.row_tok, dm.row_slot, stok, x, M, e->D.d, e->stream);
+      launch_embed<f16_t>(e->ptr<f16_t>(e->Ly.embed), pool, dm.row_tok, dm.row_slot, stok, x, M, e->D.d, e->D.V,
+                          e->stream);
       rc = run_layers<f16_t>(e, pf, M, n_rows, n_rows, max_len, attn_items, dm, log_off, step);
       break;
     case ACT_BF16:
       launch_embed<bf16_t>(e->ptr<bf16_t>(e->Ly.embed), pool, dm.row_tok, dm.row_slot, stok, x, M, e->D.d,
-                           e->stream);
+                           e->D.V, e->stream);
       rc = run_layers<bf16_t>(e, pf, M, n_rows, n_rows, max_len, attn_items, dm, log_off, step);
       break;
     default:
-      launch_embed<float>(e->ptr<float>(e->Ly.embed), pool, dm.row_tok, dm.row_slot, stok, x, M, e->D.d, e->stream);
+      launch_embed<float>(e->ptr<float>(e->Ly.embed), pool, dm.row_tok, dm.row_slot, stok, x, M, e->D.d, e->D.V,
+                          e->stream);
       rc = run_layers<float>(e, pf, M, n_rows, n_rows, max_len, attn_items, dm, log_off, step);
   }
   if (rc) return rc;

@@ -76,10 +76,11 @@ struct Epi {
 // ---------------------------------------------------------------- launches
 
 // x[M, d] (fp32) = embedding rows; token of row m: pool[tok_idx[m]] if
-// tok_idx[m] >= 0, else slot_tok[row_slot[m]].
+// tok_idx[m] >= 0, else slot_tok[row_slot[m]].  Tokens outside 0..V - 1 give
+// rows of NaN.
 template <typename T>
 void launch_embed(const T *E, const int32_t *pool, const int32_t *tok_idx, const int32_t *row_slot,
-                  const int32_t *slot_tok, float *x, int M, int d, hipStream_t s);
+                  const int32_t *slot_tok, float *x, int M, int d, int V, hipStream_t s);
 
 // Optionally folds split-K partials into the residual (x[r] += sum_s part[s][r]),
 // then y[j] = rmsnorm(x[src(j)]) * g where src(j) = rows ? rows[j] : j.

@@ -11,17 +11,23 @@ namespace lp {
 // One workgroup per row.  The row is read in 16-byte pieces, four per thread
 // requested before any is stored, so a row of up to 4,096 16-bit (2,048
 // fp32) values costs one memory round trip; rows whose length is not a
-// multiple of the piece take the element loop.
+// multiple of the piece take the element loop.  A row of logits that holds
+// nothing but NaN has no largest one, and its token (argmax_kernel's 0x7fffffff)
+// is outside the vocabulary: such a token embeds as NaN, without a read.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(const T *__restrict__ E, const int32_t *pool,
                                                     const int32_t *tok_idx, const int32_t *row_slot,
                                                     const int32_t *slot_tok, float *__restrict__ x,
-                                                    int d) {
+                                                    int d, int V) {
   const int m = blockIdx.x;
   const int ti = tok_idx[m];
   const int tok = ti >= 0 ? pool[ti] : slot_tok[row_slot[m]];
-  const T *src = E + (int64_t)tok * d;
   float *dst = x + (int64_t)m * d;
+  if ((uint32_t)tok >= (uint32_t)V) {
+    for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = NAN;
+    return;
+  }
+  const T *src = E + (int64_t)tok * d;
   constexpr int EV = 16 / sizeof(T);  // elements per 16-byte piece
   constexpr int U = 4;
   if (d % EV == 0) {
@@ -49,9 +55,9 @@ __global__ __launch_bounds__(256) void embed_kernel(const T *__restrict__ E, con
 
 template <typename T>
 void launch_embed(const T *E, const int32_t *pool, const int32_t *tok_idx, const int32_t *row_slot,
-                  const int32_t *slot_tok, float *x, int M, int d, hipStream_t s) {
+                  const int32_t *slot_tok, float *x, int M, int d, int V, hipStream_t s) {
   if (M <= 0) return;
-  embed_kernel<T><<<M, 256, 0, s>>>(E, pool, tok_idx, row_slot, slot_tok, x, d);
+  embed_kernel<T><<<M, 256, 0, s>>>(E, pool, tok_idx, row_slot, slot_tok, x, d, V);
 }
 
 // ------------------------------------------------------------------ RMSNorm
@@ -967,7 +973,7 @@ void launch_fill_f32(float *dst, int64_t n, float v, hipStream_t s) {
 
 #define INST(T)                                                                                   \
   template void launch_embed<T>(const T *, const int32_t *, const int32_t *, const int32_t *,     \
-                                const int32_t *, float *, int, int, hipStream_t);                 \
+                                const int32_t *, float *, int, int, int, hipStream_t);            \
   template void launch_rmsnorm<T>(float *, const float *, int, int64_t, const int32_t *,          \
                                   const float *, T *, int, int, float, hipStream_t);              \
   template void launch_init_weight<T>(T *, uint32_t, uint32_t, uint32_t, int64_t, int64_t, float, \

@@ -7,6 +7,8 @@
 * the run's schedule and token timestamps replayed through the oracle's
   scheduler; per-request latency accounting identities.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -125,6 +127,42 @@ def test_tiny_degenerate_requests():
         assert np.max(np.abs(got - logits)) <= 1e-4
         np.testing.assert_array_equal(eng.result(r.id)["tokens"], toks)
     check_accounting(eng, reqs)
+
+
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+def test_tokens_of_all_nan_logits_embed_without_a_read(act):
+    """A model whose final gain is NaN: no logit is a largest one, every token
+    is 0x7fffffff, and the decode steps that feed it back read no embedding row
+    (the embedding is NaN instead).  Forced tokens are embedded as ever: the
+    same engine with sound weights and the cache blocks that held the NaN then
+    serves what a fresh engine serves."""
+    shape = synth.SHAPES["tiny"]
+    if act != "f32":
+        shape = dataclasses.replace(shape, dtype=lp.LP_BF16)
+    flags = lp.LP_FLAG_KEEP_LOGITS | (lp.LP_FLAG_BF16_ACTIVATIONS if act == "bf16" else 0)
+    rng = np.random.default_rng(21)
+    reqs = [synth.Request(i, rng.integers(0, shape.vocab, size=n).astype(np.int32), 5) for i, n in enumerate((3, 70))]
+
+    def engine():
+        return lp.Engine(lp.make_config(shape), lp.EngineOptions(2, 80, 0, 128, 0, flags))
+
+    def serve(eng):
+        eng.submit(reqs)
+        eng.run(lp.LP_CLOSED_LOOP, 2)
+        return [eng.result(r.id)["tokens"] for r in reqs], [eng.logits(r.id, k) for r in reqs for k in range(5)]
+
+    good, bad = synth.model_weights(shape, 31), synth.model_weights(shape, 31)
+    bad["final_norm"] = np.full_like(bad["final_norm"], np.nan)
+    blobs = [synth.weights_blob(shape, w) for w in (good, bad)]
+    eng, fresh = engine(), engine()
+    eng.load_weights(blobs[1])
+    toks, logits = serve(eng)
+    assert all((t == 0x7FFFFFFF).all() for t in toks) and all(np.isnan(l).all() for l in logits)
+    eng.load_weights(blobs[0])
+    fresh.load_weights(blobs[0])
+    for a, b in zip(serve(eng), serve(fresh)):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
 
 
 def mixed_requests(vocab, n, seed, max_in=130, min_out=8, max_out=20):
