@@ -177,6 +177,35 @@ def test_sample_kernel_edges(V, pad, shift):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("V", [5000, 33000])
+def test_top_k_ties_zeros_of_either_sign(V):
+    """-0 and +0 are equal logits: where the top_k-th largest is a zero, every
+    zero is a candidate, whatever its sign and whichever sign a lane met first.
+    Few, some and many zeros (the LDS draw, the list, past the list), with and
+    without larger logits, below them masked or ordinary ones."""
+    import torch
+    rng = np.random.default_rng(V)
+    rows, logits = [], []
+    for i in range(96):
+        n_zero = (60, 600, 3000, V)[i % 4]
+        l = (-np.abs(rng.standard_normal(V)) - 0.5 if i % 8 < 4 else np.full(V, -np.inf)).astype(np.float32)
+        at = rng.permutation(V)
+        l[at[:n_zero]] = np.where(rng.random(n_zero) < 0.2, np.float32(0.0), np.float32(-0.0))
+        big = 10 if i % 3 == 0 else 0
+        l[at[:big]] = 1.0 + rng.random(big).astype(np.float32)
+        logits.append(l)
+        rows.append((1.0, (50, 12)[i % 5 == 0], (1.0, 0.9)[i % 2], (int(rng.integers(0, 2**32)), 1), (i, 0, 7)))
+    prm = torch.tensor(lp.sample_params_array(rows), device="cuda")
+    tok = torch.full((len(rows),), -1, dtype=torch.int32, device="cuda")
+    lp.op_sample(torch.tensor(np.stack(logits), device="cuda"), prm, tok)
+    torch.cuda.synchronize()
+    got = tok.cpu().numpy()
+    kinds = [check(logits[i].astype(np.float64), t, k, p, SP.draw_u24(key, ctr), int(got[i]))
+             for i, (t, k, p, key, ctr) in enumerate(rows)]
+    assert kinds.count("exact") >= len(kinds) - 1
+
+
+@pytest.mark.gpu
 def test_sample_kernel_nan_rows_take_the_histogram_selection():
     """A NaN is no maximum, weighs 0 and is never drawn; rows that hold one
     select their top_k on histograms, where it counts as a largest value: a
