@@ -159,18 +159,24 @@ void launch_rmsnorm(float *x, const float *part, int n_part, int64_t part_stride
 // so a 128,256-entry row costs four memory round trips.  One CU's vector
 // units, not its loads, bound such a pass (a row is 2,004 wave instructions
 // for every instruction an element takes, 0.8 us on four SIMDs), so a full
-// batch of steps runs without bounds checks.
-constexpr int ROW_W = 16, ROW_T = ROW_W * 64, ROW_STEP = 256, ROW_U = 8;
+// batch of steps runs without bounds checks.  The loads ask for the alignment
+// of a float only, which is all that a 16-byte global load needs, so rows of
+// any stride take them.
+constexpr int ROW_W = 16, ROW_T = ROW_W * 64, ROW_STEP = 256, ROW_U = 8, ROW_UT = 2;
 struct RowPart {
   const float *row;
   int beg, end;  // this wave's elements
-  bool vec;      // the row's 16-byte pieces are aligned
 };
 __host__ __device__ inline int row_chunk(int V) { return (V + ROW_W * ROW_STEP - 1) / (ROW_W * ROW_STEP) * ROW_STEP; }
 __device__ __forceinline__ RowPart row_part(const float *logits, int64_t ld, int m, int V) {
   const int chunk = row_chunk(V), w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int beg = min(V, w * chunk);
-  return {logits + (int64_t)m * ld, beg, min(V, beg + chunk), ld % 4 == 0 && ((uintptr_t)logits & 15) == 0};
+  return {logits + (int64_t)m * ld, beg, min(V, beg + chunk)};
+}
+__device__ __forceinline__ float4 row_load16(const float *p) {
+  typedef float f4_t __attribute__((ext_vector_type(4), aligned(4)));
+  const f4_t v = *(const f4_t *)p;
+  return make_float4(v[0], v[1], v[2], v[3]);
 }
 __device__ __forceinline__ float4 row_load4(const RowPart &R, int c, float fill) {
   float4 v;
@@ -188,22 +194,36 @@ __device__ __forceinline__ void row_walk(const RowPart &R, F f, G g) {
   const int lane = threadIdx.x & 63;
   int batch = 0;
   for (int c0 = R.beg; c0 < R.end; c0 += ROW_U * ROW_STEP, ++batch) {
-    if (R.vec && c0 + ROW_U * ROW_STEP <= R.end) {
+    if (c0 + ROW_U * ROW_STEP <= R.end) {
       float4 v[ROW_U];
 #pragma unroll
-      for (int u = 0; u < ROW_U; ++u) v[u] = *(const float4 *)(R.row + c0 + u * ROW_STEP + lane * 4);
+      for (int u = 0; u < ROW_U; ++u) v[u] = row_load16(R.row + c0 + u * ROW_STEP + lane * 4);
 #pragma unroll
       for (int u = 0; u < ROW_U; ++u) f(c0 + u * ROW_STEP + lane * 4, v[u], std::integral_constant<int, 4>());
     } else {
-      for (int u = 0; u < ROW_U; ++u) {
-        const int c = c0 + u * ROW_STEP + lane * 4;
-        f(c, row_load4(R, c, -INFINITY), min(4, max(0, R.end - c)));
+      // the last steps, two in flight (four spill the sampler's registers): the
+      // same loads, held to the row's last whole piece, and a piece that the
+      // row ends in by elements.  Loaded by elements one step at a time, argmax
+      // of 64 x 20,000 took 7.2 us for 3.7, of 50,257 (rows off 16 bytes) 13.8
+      // for 4.8.
+#pragma unroll 1
+      for (int c1 = c0; c1 < R.end; c1 += ROW_UT * ROW_STEP) {
+        float4 v[ROW_UT];
+        if (R.end >= 4) {
+#pragma unroll
+          for (int u = 0; u < ROW_UT; ++u) v[u] = row_load16(R.row + min(c1 + u * ROW_STEP + lane * 4, R.end - 4));
+        }
+#pragma unroll
+        for (int u = 0; u < ROW_UT; ++u) {
+          const int c = c1 + u * ROW_STEP + lane * 4;
+          if (c + 4 > R.end) v[u] = row_load4(R, c, -INFINITY);
+          f(c, v[u], min(4, max(0, R.end - c)));
+        }
       }
     }
     g(batch);
   }
 }
-
 // This lane's largest logit, where its first 16-byte piece that holds it
 // starts, and whether it met a NaN (which no comparison picks).
 struct RowBest {
@@ -255,8 +275,8 @@ __device__ __forceinline__ int row_first(const RowPart &R, const RowBest &b, flo
 }
 
 // One workgroup per row: the maximum, then the lowest index that holds it,
-// found again in the one piece its lane remembers.  64 rows of 128,256: 15.7
-// -> 8.7 us (an index was merged with every element before).
+// found again in the one piece its lane remembers.  64 rows of 128,256: 15.5
+// -> 8.0 us (an index was merged with every element before).
 __global__ __launch_bounds__(ROW_T) void argmax_kernel(const float *__restrict__ logits, int64_t ld, int V,
                                                        const int32_t *out_slot, int32_t *slot_tok, int32_t *tok_log) {
   __shared__ float sv[ROW_W];
@@ -328,8 +348,10 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
 //    one that adds up the pieces of everything heavier than the chosen bin and
 //    lists that bin's elements, which the remaining levels refine in LDS.
 // Candidate sets of at most SP_SMALL are settled by direct sums.  64 rows of
-// 128,256 logits: greedy 23.7 -> 9.6 us, temperature 82.7 -> 26.6, top-k 40
-// 68.0 -> 28.3, top-p 0.9 157 -> 75.6, top-k 50 with top-p 0.95 90.5 -> 33.5.
+// 128,256 logits, in a graph of launches, against five passes with an index
+// merge, an atomic or a 64-bit shuffle an element: greedy 23.4 -> 9.0 us,
+// temperature 82.7 -> 25.5, top-k 40 68.2 -> 27.4, top-p 0.9 157 -> 74.4, top-k 50
+// with top-p 0.95 90.8 -> 32.9.
 // Keys in the order of the values: x + 0 makes the zeros of either sign one key,
 // as they are one value to the float comparisons that choose a lane's maximum.
 __device__ __forceinline__ uint32_t order_key(float x) {

@@ -351,6 +351,26 @@ def test_argmax_strides_and_tails(V, ld):
     assert out.cpu().numpy().tolist() == [int(np.argmax(r[:V])) for r in full]
 
 
+@pytest.mark.parametrize("V", [1, 3, 4, 5, 255, 259, 513, 4097, 20001, 33030])
+def test_argmax_last_steps(V):
+    """The walk's last steps: rows shorter than a piece, rows that end inside a
+    piece or a step, at every stride and offset of a float; the largest value in
+    each of the row's last places, larger ones right behind the row."""
+    rows, strides = 8, [V + pad for pad in range(4)]
+    for ld in strides:
+        for shift in range(4):
+            buf = torch.full((rows * ld + 8,), 1e30, dtype=torch.float32, device=DEV)
+            L = buf[shift:shift + rows * ld].view(rows, ld)[:, :V]
+            L.copy_(torch.arange(V, dtype=torch.float32).expand(rows, V) * -1e-3)
+            want = [max(0, V - 1 - i) for i in range(rows)]
+            for i, w in enumerate(want):
+                L[i, w] = 2.0
+            out = torch.empty(rows, dtype=torch.int32, device=DEV)
+            lp.op_argmax(L, out)
+            torch.cuda.synchronize()
+            assert out.cpu().tolist() == want, (ld, shift)
+
+
 @pytest.mark.parametrize("V,shift", [(3, 0), (256, 0), (5000, 0), (5000, 1), (70000, 0)])
 def test_argmax_special_values(V, shift):
     """NaN is never chosen, -inf only where nothing is larger, zeros of either
