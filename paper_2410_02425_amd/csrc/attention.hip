@@ -709,6 +709,10 @@ __device__ __forceinline__ typename Mfma<T>::v8 pack8(const float *p) {
   return v;
 }
 
+// Base-2 score past which the maximum is taken off before the scale: up to here
+// a rounded mc is within 2^-13, an eighth of the f16 rounding of a weight of 1.
+constexpr float PFA_LARGE = 4096.f;
+
 template <typename T, int HD, int QW, int KG>
 __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const T *__restrict__ q,
                                                                           T *__restrict__ out,
@@ -801,6 +805,7 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
   // running maximum (raw scores), the score past which it moves, its base-2
   // value; this half's share of the sum
   float mref = -INFINITY, mc = 0.f, lsum = 0.f;
+  bool large = false;  // wave-uniform: a row's |mc| is past PFA_LARGE
   const float c2 = rsqrtf((float)HD) * 1.44269504088896341f;
   // fragment addresses: K row with bits 2 and 3 swapped, V row l32 (+ 32 t)
   const int krow = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
@@ -868,11 +873,24 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
       const float corr = nm == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mref - nm) * c2);
       mref = nm;
       mc = nm == -INFINITY ? 0.f : nm * c2;  // a row that has seen no key yet
+      large = __any(fabsf(mc) > PFA_LARGE);
       lsum *= corr;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[t][r] *= corr;
+    }
+    // s c2 - mc in one FMA is off 0 at the maximum by what mc's rounding left
+    // out, up to half a unit of mc: large scores have the maximum taken off
+    // before the product instead
+    float mo = mc;
+    if (large) {
+      const float m0 = mref == -INFINITY ? 0.f : mref;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[t][r] -= m0;
+      mo = 0.f;
     }
     v8 pb[4];
 #pragma unroll
@@ -882,7 +900,7 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
         float p[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-          p[r] = __builtin_amdgcn_exp2f(fmaf(s[t][u * 8 + r], c2, -mc));
+          p[r] = __builtin_amdgcn_exp2f(fmaf(s[t][u * 8 + r], c2, -mo));
           lsum += p[r];
         }
         pb[t * 2 + u] = pack8<T>(p);

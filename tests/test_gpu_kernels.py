@@ -562,6 +562,43 @@ def test_prefill_attention_tiles(dtype, Hq, Hkv, hd, lens, shift):
         r0 += n
 
 
+@pytest.mark.parametrize("dtype,lo,hi", [("f16", 2, 37), ("bf16", 2, 100)])
+@pytest.mark.parametrize("heads,n", [(8, 300), (40, 700)])    # one and two key groups
+def test_prefill_attention_scores_of_any_size(dtype, lo, hi, heads, n):
+    """Scores up to 2^hi, where a float's spacing is far more than a power of
+    two of the softmax: the largest score's weight stays 1 (a product with the
+    scale that is rounded apart from the one it is compared with leaves up to
+    half a spacing, which overflows or empties the row).  Every head has its own
+    size, and q and k are such that each score is exact in fp32: the output is
+    the mean of V over the largest keys so far, to one rounding of the result
+    and of the weights."""
+    rng = np.random.default_rng(n)
+    hd, tdt = 128, HALF[dtype]
+    q = np.ones((n, heads, hd), np.float32)
+    e = np.linspace(lo, hi - 7, heads).astype(int)            # 128 dims add 7 bits
+    q *= (2.0 ** (e // 2))[None, :, None]
+    steps = rng.integers(64, 128, size=(n, heads)).astype(np.float32) * rng.choice([-1.0, 1.0], size=(n, heads))
+    lens = [n]
+    (kc, vt, bt), Ks, Vs = make_paged_cache(rng, lens, heads, hd, tdt)
+    k = np.repeat((steps * (2.0 ** (e - e // 2 - 6))[None, :])[:, :, None], hd, axis=2)
+    for b in range(-(-n // 64)):
+        m = min(64, n - b * 64)
+        kc[int(bt[0, b]), :, :m] = to_dev(k[b * 64:b * 64 + m].transpose(1, 0, 2).copy(), tdt)
+    qd = to_dev(q, tdt)
+    assert torch.isfinite(qd).all() and torch.isfinite(kc).all()
+    out = torch.empty_like(qd)
+    start = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    lp.op_prefill_attention(qd, out, kc, vt, bt, start, torch.zeros(1, dtype=torch.int32, device=DEV), n, heads)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    args = (q.astype(np.float64), k.astype(np.float64))
+    ref = T.attention(*args, Vs[0].astype(np.float64), np.arange(n), np.arange(n), heads)
+    mag = T.attention(*args, np.abs(Vs[0].astype(np.float64)), np.arange(n), np.arange(n), heads)
+    bad = ~(np.abs(got - ref) <= attention_tol(dtype, ref, mag))
+    n_bad, heads_bad = int(bad.sum()), sorted(set(np.argwhere(bad)[:, 1].tolist()))
+    assert n_bad == 0, heads_bad
+
+
 def test_zero_row_calls_through_the_binding():
     """Empty device tensors (null data pointers) through the binding: nothing
     is launched and the outputs of other calls are untouched."""
