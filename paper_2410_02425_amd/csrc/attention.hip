@@ -9,7 +9,10 @@
 // triples are merged by a combine pass (log-sum-exp rescaling).
 //
 // Prefill: causal attention of packed prompt rows, one workgroup per 128 query
-// rows (fp32: 64) of one (sequence, head), online softmax over 64-key blocks.
+// rows (fp32, and steps of prompts up to 64 tokens: 64) of one (sequence, head),
+// online softmax over 64-key blocks.
+#include <type_traits>
+
 #include "device.hpp"
 
 namespace lp {
@@ -673,19 +676,18 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const T *__restrict__
 //   The running maximum is moved (and O and the sum rescaled) in the blocks
 //   that raise it for one of the wave's rows, so that a row's largest
 //   probability is exactly 1 before it is rounded to 16 bits.  Moving it only
-//   where a score exceeds it by 2^8 ran 5% faster (547 tokens 13.7 against 14.4
-//   us, three prompts around 2,100 298 against 313; the figures below are with
-//   it) and put the result 2.7% further from 64 bits (three prompts of 900,
-//   bf16: 0.00206 against 0.00200).
+//   where a score exceeds it by 2^8 ran 5% faster (three prompts around 2,100
+//   tokens 298 against 313 us) and put the result 2.7% further from 64 bits
+//   (three prompts of 900, bf16: 0.00206 against 0.00200).
 // 32 rows a wave read half the LDS bytes per flop that 16 did (the 16-row
 // kernel needed 256 B a clock and CU, all that LDS delivers), and the vector
 // work of the softmax is what is left beside the MFMAs.  8B heads, fp16, 16-row
-// waves against this kernel: one prompt of 547 tokens 20.6 -> 15.5 us, 4,096
-// tokens 276 -> 169, three of 8,400 together 542 -> 328 (880 TFLOP/s, the
-// clock down to 1.8 GHz); 64 prompts of 600 640 -> 484.  Deeper staging (three
-// to five stages), the next block's scores or the output products interleaved
-// with the softmax by hand, and 64- or 256-row tiles all measured the same or
-// slower.
+// waves against this kernel (in graphs of launches): one prompt of 300 tokens
+// 12.0 -> 10.5 us, 547 19.0 -> 14.4, 1,300 42.9 -> 27.2, 4,096 252 -> 166 (830
+// TFLOP/s, the clock down to 1.8 GHz); 8 prompts of 1,000 235 -> 106, 64 of 600
+// 537 -> 372.  Deeper staging (three to five stages) and the next block's scores
+// or the output products interleaved with the softmax by hand all measured the
+// same or slower.
 // KG key groups: group k of the waves takes every KG-th key block with its own
 // stages, and the groups' (maximum, sum, O) meet in LDS at the end.
 // Grid: x = head, dealt so that the heads of one KV head run on one XCD and
@@ -709,6 +711,46 @@ __device__ __forceinline__ typename Mfma<T>::v8 pack8(const float *p) {
   return v;
 }
 
+// Stores a 32-dim tile of O^T times inv: a lane holds one row's dims 8 (r / 4) +
+// 4 hh + r % 4.  The halves of the wave trade every other four dims, so that a
+// lane stores eight consecutive dims at once (dst: the row's tile), from a base
+// that is aligned for them; all lanes call, `valid` ones store.
+template <typename T>
+__device__ __forceinline__ void store_o32(T *dst, const floatx16_t &o, float inv, int hh, bool valid) {
+  typedef uint32_t u4_t __attribute__((ext_vector_type(4), aligned(4)));
+  const bool al4 = ((uintptr_t)dst & 3) == 0;
+#pragma unroll
+  for (int r8 = 0; r8 < 2; ++r8) {
+    uint32_t w[2][2];  // dims 16 r8 + 8 i + 4 hh + {0, 1}, {2, 3}
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const T lo = Act<T>::st(o[r8 * 8 + i * 4 + e * 2] * inv), hi = Act<T>::st(o[r8 * 8 + i * 4 + e * 2 + 1] * inv);
+        w[i][e] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | (uint32_t)__builtin_bit_cast(uint16_t, hi) << 16;
+      }
+    u4_t v;  // dims 16 r8 + 8 hh ..
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const auto t = __builtin_amdgcn_permlane32_swap(w[0][e], w[1][e], false, false);
+      v[e] = t[0];
+      v[e + 2] = t[1];
+    }
+    T *d = dst + r8 * 16 + hh * 8;
+    if (valid) {
+      if (al4) {
+        *(u4_t *)d = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          d[2 * e] = __builtin_bit_cast(T, (uint16_t)v[e]);
+          d[2 * e + 1] = __builtin_bit_cast(T, (uint16_t)(v[e] >> 16));
+        }
+      }
+    }
+  }
+}
+
 // Base-2 score past which the maximum is taken off before the scale: up to here
 // a rounded mc is within 2^-13, an eighth of the f16 rounding of a weight of 1.
 constexpr float PFA_LARGE = 4096.f;
@@ -727,6 +769,7 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
   constexpr int STAGE = 2 * PB;
   constexpr int ND = PB / 1024 / QW;     // 1 KB copies per wave and block, K and V each
   __shared__ __attribute__((aligned(1024))) char lds[KG * 2 * STAGE];
+  static_assert(QW * 64 >= HD, "a V row for every thread of a key group");
   static_assert(KG == 1 || (KG - 1) * QW * (NT * 16 + 2) * 256 <= KG * 2 * STAGE, "space of the group merge");
   const int xh = blockIdx.x;
   const int h = n_heads % 8 == 0 ? xh % 8 * (n_heads / 8) + xh / 8 : xh;
@@ -819,22 +862,29 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (it == nit - 1 && nblk * 64 > len) {
       // the sequence ends inside the last block: V entries past it are stale
-      // or uninitialised, their weight is 0 but 0 * NaN is not
+      // or uninitialised, their weight is 0 but 0 * NaN is not.  The piece of a
+      // row that the end falls into is masked, those behind it are cleared
+      // without a read (a read, mask and write for every piece is a chain of
+      // LDS round trips: one prompt of 100 tokens 7.2 us for 6.9).
       if ((nblk - 1) % KG == kg) {
         const int kvalid = len - (nblk - 1) * 64;
         char *vs = lds + kg * 2 * STAGE + (it & 1) * STAGE + PB;
-        for (int e = qw * 64 + lane; e < HD * 8; e += QW * 64) {
-          const int row = e >> 3, key0 = ((e & 7) ^ ((row >> 1) & 7)) * 8;
-          if (key0 + 8 > kvalid) {
-            u32x4_tt v = *(const u32x4_tt *)(vs + e * 16);
+        const int row = qw * 64 + lane;
+        if (QW * 64 == HD || row < HD) {
+          char *p = vs + row * KV_BLOCK * 2 + ((kvalid >> 3) ^ ((row >> 1) & 7)) * 16;
+          u32x4_tt v = *(const u32x4_tt *)p;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-              const uint32_t lo = key0 + 2 * w < kvalid ? 0xFFFFu : 0u;
-              const uint32_t hi = key0 + 2 * w + 1 < kvalid ? 0xFFFF0000u : 0u;
-              v[w] &= (lo | hi);
-            }
-            *(u32x4_tt *)(vs + e * 16) = v;
+          for (int w = 0; w < 4; ++w) {
+            const uint32_t lo = 2 * w < (kvalid & 7) ? 0xFFFFu : 0u;
+            const uint32_t hi = 2 * w + 1 < (kvalid & 7) ? 0xFFFF0000u : 0u;
+            v[w] &= (lo | hi);
           }
+          *(u32x4_tt *)p = v;
+        }
+#pragma unroll
+        for (int e = qw * 64 + lane; e < HD * 8; e += QW * 64) {
+          const int r = e >> 3, key0 = ((e & 7) ^ ((r >> 1) & 7)) * 8;
+          if (key0 > kvalid) *(u32x4_tt *)(vs + e * 16) = u32x4_tt{0, 0, 0, 0};
         }
       }
       __syncthreads();
@@ -946,22 +996,137 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
   }
   // o[t][r]: dim 32 t + 8 (r / 4) + 4 hh + r % 4 of this lane's query
   const float inv = 1.0f / half_swap_sum(lsum);
-  if (qpos < len) {
-    T *orow = out + ((int64_t)(row0 + qpos) * n_heads + h) * HD + hh * 4;
-    const bool al8 = ((uintptr_t)out & 7) == 0;
+  T *orow = out + ((int64_t)(row0 + qpos) * n_heads + h) * HD;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+  for (int t = 0; t < NT; ++t) store_o32(orow + t * 32, o[t], inv, hh, qpos < len);
+}
+
+// Prompts of at most one cache block (64 tokens): a wave owns 32 query rows of a
+// (sequence, head), with the products and layouts of the kernel above and
+// nothing online in the softmax; queries 0..31 need the first 32 keys alone.
+//   * STAGED: a workgroup is the two waves of a (sequence, head), with the block
+//     copied into LDS once for both by whole 1 KB requests (the fragments ask
+//     for 32 bytes of a row at a time, and memory bounds a step of many waves).
+//   * Not STAGED, prompts of at most 32 tokens: one wave, which requests all its
+//     K and V fragments straight from the cache at once; staging only adds a
+//     barrier and LDS.
+// The 128-row tiles above leave half the waves or more of such a prompt without
+// a row.  8B heads, fp16, 64-row tiles of 16-row waves, those tiles, and these:
+// 64 prompts of 16 tokens 19.5, 21.1 and 9.3 us; of 33 21.4, 23.8 and 15.3; of
+// 64 25.7, 26.0 and 19.5; 16 of 60 8.0, 8.9 and 7.2; one prompt of 32 5.4, 5.4
+// and 4.2.  40 heads of their own K and V, 64 prompts of 64: 29.8, 36.9 and 29.8.
+template <typename T, int HD, bool STAGED>
+__global__ __launch_bounds__(STAGED ? 128 : 64, 3) void prefill_attn_block_kernel(
+    const T *__restrict__ q, T *__restrict__ out, const int32_t *seq_start, const int32_t *seq_slot, KVCache kv,
+    int layer, int n_heads) {
+  typedef typename Mfma<T>::v8 v8;
+  constexpr int KS = HD / 16, NT = HD / 32, PB = 64 * HD * 2;
+  __shared__ __attribute__((aligned(1024))) char lds[STAGED ? 2 * PB : 16];
+  const int xh = blockIdx.x;
+  // heads that share K and V on one XCD; else in the cache's order
+  const int h = n_heads % 8 == 0 && n_heads > kv.n_kv_heads ? xh % 8 * (n_heads / 8) + xh / 8 : xh;
+  const int j = blockIdx.y;
+  const int qt = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int row0 = seq_start[j];
+  const int len = seq_start[j + 1] - row0;
+  if (len <= 0) return;
+  const int64_t base = kv_block_base(kv, layer, seq_slot[j], 0, h / (n_heads / kv.n_kv_heads));
+  const T *kb = (const T *)kv.k + base, *vb = (const T *)kv.v + base;
+  const int l32 = lane & 31, hh = lane >> 5, qpos = qt * 32 + l32;
+  const int krow = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
+  // 16-byte pieces of K and V rows are XOR-swizzled in LDS, as above
+  constexpr int CK = HD / 8, KR = 1024 / (HD * 2);
+  auto swz = [](int row) __attribute__((always_inline)) { return CK == 16 ? row & 15 : (row >> 1) & 7; };
+  if constexpr (STAGED) {
+    const uint32_t lds0 = lds_addr(lds);
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        T v[4];
+    for (int c = 0; c < PB / 2048; ++c) {
+      const int n = qt * (PB / 2048) + c, kr = n * KR + lane / CK, vr = n * 8 + (lane >> 3);
+      // copies of keys past the sequence alone are left out: masked below
+      if (n * KR < len) dma16s(kb, kr * HD * 2 + ((lane % CK) ^ swz(kr)) * 16, lds0 + n * 1024);
+      dma16s(vb, vr * KV_BLOCK * 2 + ((lane & 7) ^ ((vr >> 1) & 7)) * 16, lds0 + PB + n * 1024);
+    }
+  }
+  const T *qr = q + ((int64_t)(row0 + min(qpos, len - 1)) * n_heads + h) * HD + hh * 8;
+  v8 qb[KS];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = Act<T>::st(o[t][r4 * 4 + e] * inv);
-        T *dst = orow + t * 32 + r4 * 8;
-        if (al8)
-          *(uint2 *)dst = __builtin_bit_cast(uint2, *(const uint2 *)v);
-        else
-          for (int e = 0; e < 4; ++e) dst[e] = v[e];
+  for (int k = 0; k < KS; ++k) qb[k] = load8<T>(qr + k * 16);
+  if constexpr (STAGED) asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  auto rows = [&](auto tiles) __attribute__((always_inline)) {
+    constexpr int TK = decltype(tiles)::value;  // 32-key tiles
+    v8 ka[KS], va[2][NT];
+    if constexpr (!STAGED) {
+#pragma unroll
+      for (int k = 0; k < KS; ++k) ka[k] = load8<T>(kb + krow * HD + k * 16 + hh * 8);
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) va[k][t] = load8<T>(vb + (t * 32 + l32) * KV_BLOCK + k * 16 + hh * 8);
+    }
+    floatx16_t s[TK];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < TK; ++t) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        v8 a;
+        if constexpr (STAGED) a = *(const v8 *)(lds + (t * 32 + krow) * HD * 2 + (((hh ^ swz(krow)) << 4) ^ (k << 5)));
+        else a = ka[k];
+        s[t] = Mfma<T>::m32(a, qb[k], s[t]);
       }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        if (t * 32 + (r >> 3) * 16 + hh * 8 + (r & 7) > qpos) s[t][r] = -INFINITY;
+        mx = fmaxf(mx, s[t][r]);
+      }
+    }
+    mx = half_swap_max(mx);
+    const float m0 = mx == -INFINITY ? 0.f : mx, c2 = rsqrtf((float)HD) * 1.44269504088896341f;
+    float lsum = 0.f;
+    v8 pb[TK * 2];
+    // V entries past the sequence are stale or uninitialised: their weight is 0
+    // but 0 * NaN is not
+    u32x4_tt keep[TK * 2];
+#pragma unroll
+    for (int k = 0; k < TK * 2; ++k) {
+      float p[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        p[r] = __builtin_amdgcn_exp2f((s[k >> 1][(k & 1) * 8 + r] - m0) * c2);
+        lsum += p[r];
+      }
+      pb[k] = pack8<T>(p);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int key = k * 16 + hh * 8 + 2 * w;
+        keep[k][w] = (key < len ? 0xFFFFu : 0u) | (key + 1 < len ? 0xFFFF0000u : 0u);
+      }
+    }
+    const float inv = 1.0f / half_swap_sum(lsum);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      floatx16_t o;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] = 0.f;
+#pragma unroll
+      for (int k = 0; k < TK * 2; ++k) {
+        u32x4_tt v;
+        if constexpr (STAGED)
+          v = *(const u32x4_tt *)(lds + PB + (t * 32 + l32) * KV_BLOCK * 2 +
+                                  (((hh ^ ((l32 >> 1) & 7)) << 4) ^ (k << 5)));
+        else
+          v = __builtin_bit_cast(u32x4_tt, va[k][t]);
+        o = Mfma<T>::m32(__builtin_bit_cast(v8, v & keep[k]), pb[k], o);
+      }
+      store_o32(out + ((int64_t)(row0 + qpos) * n_heads + h) * HD + t * 32, o, inv, hh, qpos < len);
+    }
+  };
+  if (qt == 0) {
+    rows(std::integral_constant<int, 1>());
+  } else if constexpr (STAGED) {
+    if (len > 32) rows(std::integral_constant<int, 2>());
   }
 }
 
@@ -983,6 +1148,7 @@ template <typename T, int HD>
 static void launch_prefill_hd(const T *q, T *out, const int32_t *seq_start, const int32_t *seq_slot, int n_seq,
                               int max_len, const KVCache &kv, int layer, int n_heads, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
+    // Prompts of one cache block have kernels of their own (figures there).
     // Two key groups for one prompt whose workgroups are too few for two on
     // every CU but enough to use most CUs: each CU's second set of waves then
     // comes from the key groups, and the longest tile walks half its blocks
@@ -993,7 +1159,13 @@ static void launch_prefill_hd(const T *q, T *out, const int32_t *seq_start, cons
     // 169 against 187), and with several prompts the grid's upper bound says
     // little about the live tiles (3 x 400 tokens: 16.5 against 19.2).
     const int64_t wgs = (int64_t)((max_len + 127) / 128) * n_heads;
-    if (n_seq == 1 && wgs >= 160 && wgs <= 448)
+    if (max_len <= 32)
+      prefill_attn_block_kernel<T, HD, false><<<dim3(n_heads, n_seq), 64, 0, s>>>(q, out, seq_start, seq_slot, kv,
+                                                                                  layer, n_heads);
+    else if (max_len <= KV_BLOCK)
+      prefill_attn_block_kernel<T, HD, true><<<dim3(n_heads, n_seq), 128, 0, s>>>(q, out, seq_start, seq_slot, kv,
+                                                                                  layer, n_heads);
+    else if (n_seq == 1 && wgs >= 160 && wgs <= 448)
       launch_prefill_mfma<T, HD, 4, 2>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
     else
       launch_prefill_mfma<T, HD, 4, 1>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);

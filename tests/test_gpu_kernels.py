@@ -531,6 +531,12 @@ def test_prefill_attention(dtype, Hq, Hkv, hd, lens):
     ("bf16", 64, 8, 64, [385], 0),                          # the same at head_dim 64, 256 workgroups, group of 8
     ("f16", 2, 1, 128, [4230], 0),                          # more than 64 cache blocks
     ("f16", 64, 32, 128, [260], 1),                         # out off 8 bytes: element stores; two key groups
+    ("f16", 8, 8, 128, [1, 31, 32, 17], 0),                 # at most 32 tokens: K and V straight from the cache
+    ("bf16", 6, 3, 64, [32, 5], 2),                         # ... heads not a multiple of 8, out on 4 bytes
+    ("f16", 8, 2, 128, [33, 64, 1, 32, 63, 48], 0),         # at most one cache block: both waves' rows, or one's
+    ("bf16", 4, 4, 64, [64, 40], 1),                        # ... out off 4 bytes: element stores
+    ("bf16", 64, 8, 128, [64] * 9 + [33], 2),               # ... a group of 8
+    ("f16", 16, 4, 128, [65, 70, 71, 72, 73], 0),           # the end in each place of a 16-byte piece of V
 ])
 def test_prefill_attention_tiles(dtype, Hq, Hkv, hd, lens, shift):
     """Edges of the prefill attention's tiles, key groups and copies, with every
@@ -563,7 +569,7 @@ def test_prefill_attention_tiles(dtype, Hq, Hkv, hd, lens, shift):
 
 
 @pytest.mark.parametrize("dtype,lo,hi", [("f16", 2, 37), ("bf16", 2, 100)])
-@pytest.mark.parametrize("heads,n", [(8, 300), (40, 700)])    # one and two key groups
+@pytest.mark.parametrize("heads,n", [(8, 300), (40, 700), (8, 64), (8, 30)])  # one and two key groups, one block
 def test_prefill_attention_scores_of_any_size(dtype, lo, hi, heads, n):
     """Scores up to 2^hi, where a float's spacing is far more than a power of
     two of the softmax: the largest score's weight stays 1 (a product with the
