@@ -1149,14 +1149,18 @@ static void launch_prefill_hd(const T *q, T *out, const int32_t *seq_start, cons
                               int max_len, const KVCache &kv, int layer, int n_heads, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {
     // Prompts of one cache block have kernels of their own (figures there).
-    // Two key groups for one prompt whose workgroups are too few for two on
-    // every CU but enough to use most CUs: each CU's second set of waves then
-    // comes from the key groups, and the longest tile walks half its blocks
-    // (8B heads: 888 tokens, 224 workgroups, 23.7 -> 22.3 us; 1,300 tokens, 352,
-    // 34.6 -> 30.2; 1,700 tokens, 448, 44.7 -> 42.2).  Below, the merge costs
-    // what it saves (400 tokens, 128: 13.0 against 13.1; 234 tokens: 10.0
-    // against 11.1); above, two workgroups a CU overlap better (4,096 tokens:
-    // 169 against 187), and with several prompts the grid's upper bound says
+    // Two key groups for one prompt whose workgroups use half the CUs or more
+    // and would fit two to every CU: each CU's second set of waves then comes
+    // from the key groups, and the longest tile walks half its blocks (8B heads,
+    // one group against two: 400 tokens, 128 workgroups, 12.8 against 12.3 us;
+    // 547, 160, 15.6 against 14.3; 1,300, 352, 32.7 against 27.2; 2,048, 512,
+    // 55.0 against 48.8).  Below, the merge costs what it saves (384 tokens, 96:
+    // 12.2 against 12.0; 256, 64: 9.5 against 10.0); above, two workgroups a CU
+    // overlap better (2,300 tokens, 576: 64.6 against 66.4; 2,600, 672: 76
+    // against 83).  40 heads of their own K and V: 480 workgroups 42.7 against
+    // 40.2, 520 47.3 against 48.4.  64 heads, 8 of K and V, gain least: 640
+    // tokens, 320, 19.3 against 17.7; 700, 384, 20.7 against 21.6; 1,000, 512,
+    // 31.0 against 30.7.  With several prompts the grid's upper bound says
     // little about the live tiles (3 x 400 tokens: 16.5 against 19.2).
     const int64_t wgs = (int64_t)((max_len + 127) / 128) * n_heads;
     if (max_len <= 32)
@@ -1165,7 +1169,7 @@ static void launch_prefill_hd(const T *q, T *out, const int32_t *seq_start, cons
     else if (max_len <= KV_BLOCK)
       prefill_attn_block_kernel<T, HD, true><<<dim3(n_heads, n_seq), 128, 0, s>>>(q, out, seq_start, seq_slot, kv,
                                                                                   layer, n_heads);
-    else if (n_seq == 1 && wgs >= 160 && wgs <= 448)
+    else if (n_seq == 1 && wgs >= 128 && wgs <= 512)
       launch_prefill_mfma<T, HD, 4, 2>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
     else
       launch_prefill_mfma<T, HD, 4, 1>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
