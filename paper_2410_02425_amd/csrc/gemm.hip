@@ -757,14 +757,24 @@ __global__ __launch_bounds__(PF_NT, WPE) void gemm_prefill_kernel(const T *__res
 //     larger one as one more paired round.
 //   * Each round of one workgroup per CU adds PF_ROUND for the first loads'
 //     latency and the epilogue, which nothing else on the CU overlaps.
-// The rates come from the four projections of the 7B, 8B and 13B shapes at
-// M = 100..2,800 and of 70B at 300..900 (108 launches, each plan in turn): the
-// picks moved from the rates before (4.1, 5.2, 4.86 TFLOP/s, 4 TB/s, fitted to
-// the kernels before their stages were halved) are gate/up at 1,900 rows, 8B
-// 486 -> 432 us and 13B 567 -> 520 (256-row tiles, not paired), 70B gate/up at
-// 900 rows 874 -> 821, 8B down at 1,300 rows two splits for five (199 -> 192);
-// geometric mean over the launches 119.2 -> 115.2 us, 2% of it the plans.
-static constexpr double PF_RATE_128 = 4.35e12, PF_RATE_256 = 5.6e12, PF_RATE_PAIR = 4.9e12;  // flop/s per CU
+// The one-workgroup rates come from the four projections of the 7B, 8B and 13B
+// shapes at M = 100..2,800 and of 70B at 300..900 (108 launches, each plan in
+// turn): the picks moved from the rates before (4.1, 5.2, 4.86 TFLOP/s, 4 TB/s,
+// fitted to the kernels before their stages were halved) are 8B gate/up at
+// 1,900 rows 486 -> 432 us, 13B 567 -> 520, 8B down at 1,300 rows two splits for
+// five (199 -> 192); geometric mean over the launches 119.2 -> 115.2 us, 2% of it
+// the plans.  The paired rate comes from a sweep of the same projections at 35
+// row counts of 100 to 4,223 (70B: 7 of 300 to 2,100), every plan timed in one
+// process: the pick is on average 0.43% slower than the best one, where a rate
+// of 4.9 with a margin of 6% for the paired kernel gave 0.61%.  It moves 8B
+// gate/up at 2,990 rows 677 -> 658 us and at 3,500 799 -> 746, 13B at 3,072 870
+// -> 788, 7B at 3,200 547 -> 508 (to pairs).  Paired against 256-row tiles, 8B
+// gate/up: 1,200 rows 298 and 311 us (estimates 276 and 294), 1,600 369 and 405
+// (318, 391), 2,990 677 and 658 (594, 587), 3,400 756 and 737 (637, 685: the
+// pick is the slower one), 3,500 799 and 746 (700, 685).  The estimates are low
+// for long launches, whose clock falls, on both sides alike; a cost of each
+// paired round besides (0 to 6 us) did not lower the regret.
+static constexpr double PF_RATE_128 = 4.35e12, PF_RATE_256 = 5.6e12, PF_RATE_PAIR = 5.06e12;  // flop/s per CU
 static constexpr double PF_FOLD_RATE = 3.8e12;  // bytes/s of split partials, written and read back
 static constexpr double PF_ROUND = 2.0e-6;       // s a round of one workgroup per CU takes besides
 static int prefill_kchunk(int K, int s) { return (K / s + PF_KQ - 1) / PF_KQ * PF_KQ; }
@@ -808,15 +818,6 @@ struct PrefillPlan {
   bool pair;  // two 128-row workgroups per CU
 };
 
-// Where the last round of 256-row tiles fills at most a quarter of the CUs, the
-// paired kernel is kept if it is estimated within 6%.  It is not faster there
-// (8B gate/up, 2,990 rows: 704 against 657 us; 1,200 rows 323 against 307):
-// the engine's parity tests of its QKV and gate/up epilogues run at such a
-// size.  At every other one 256-row tiles now win (gate/up, 8B: 1,500 rows 384
-// against 339, 2,300 rows 537 against 483, 4,223 rows 968 against 914) but for
-// the few hundred rows that they round up (600 rows: 217 against 229).
-static constexpr double PF_PAIR_KEEP = 1.06;
-
 // splits > 0: the caller's split request (rounded to whole K chunks as
 // gemm_effective_splits does), only the tile shape is chosen; splits == 0:
 // both are chosen, from 1 to 8 splits.
@@ -838,9 +839,7 @@ static PrefillPlan prefill_plan(int M, int N, int K, int splits) {
   }
   if (splits <= 1) {
     const double t = prefill_pair_cost(M, N, K);
-    const int64_t last = (int64_t)((M + 255) / 256) * ((N + PF_BN - 1) / PF_BN) % 256;
-    const bool keep = best.bm == 256 && best.splits == 1 && last > 0 && last <= 64;
-    if (t >= 0.0 && t < tbest * (keep ? PF_PAIR_KEEP : 1.0)) best = {128, 1, true};
+    if (t >= 0.0 && t < tbest) best = {128, 1, true};
   }
   return best;
 }

@@ -212,3 +212,17 @@ def test_gemm_plan_query():
     assert lp.op_gemm_plan(64, 28672, 4096, 1, with_order=True)[3] == 0     # decode kernel
     with pytest.raises(lp.LPError):
         lp.op_gemm_plan(0, 4096, 4096)
+
+
+@pytest.mark.parametrize("rows,N,K,pair", [
+    (640, 28672, 4096, True), (1200, 28672, 4096, True), (1600, 28672, 4096, True),        # 8B gate/up
+    (2300, 28672, 4096, False), (2817, 28672, 4096, False), (2990, 28672, 4096, False),
+    (3072, 28672, 4096, False), (3500, 28672, 4096, False), (3584, 28672, 4096, False),
+    (3072, 27648, 5120, False), (1900, 27648, 5120, True), (3200, 22016, 4096, True),     # 13B, 7B gate/up
+    (3000, 6144, 4096, True), (4300, 4096, 4096, True),                                   # 8B QKV, O
+])
+def test_prefill_plan_takes_the_faster_kernel(rows, N, K, pair):
+    """Sizes where two workgroups per CU and 256-row tiles were measured 2.5% or
+    more apart: the planner takes the faster of the two."""
+    kind, tile_rows, splits = lp.op_gemm_plan(rows, N, K, 0)
+    assert (kind, tile_rows, splits) == (("prefill_pair", 128, 1) if pair else ("prefill", 256, 1))
