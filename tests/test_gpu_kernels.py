@@ -131,15 +131,24 @@ def test_gemm_16bit(M, N, K, splits, half):
     assert np.all(np.abs(got - ref) <= bound), np.max(np.abs(got - ref) / bound)
 
 
-@pytest.mark.parametrize("M,N,K,splits,ldx", [
-    (257, 272, 128, 1, 136), (300, 544, 512, 1, 520),      # four stages a K quantum: the shortest pipelines
-    (130, 300, 640, 5, 640), (600, 16400, 256, 1, 264),    # one quantum a split; two workgroups per CU
-    (66, 100, 128, 1, 1 << 27), (66, 100, 256, 2, 1 << 27),  # row strides past the stage copies' offsets
+@pytest.mark.parametrize("M,N,K,splits,ldx,plan", [
+    # four stages a K quantum: the shortest pipelines
+    (257, 272, 128, 1, 136, ("prefill", 128)), (300, 544, 512, 1, 520, ("prefill", 128)),
+    (600, 16300, 128, 1, 136, ("prefill", 256)),
+    (130, 300, 640, 5, 640, ("prefill", 128)),                           # one quantum a split
+    (600, 16400, 256, 1, 264, ("prefill", 256)),
+    # two workgroups per CU: one and two quanta, a last row tile of 104 and 92 rows
+    (4200, 16300, 128, 1, 136, ("prefill_pair", 128)), (1500, 12000, 256, 1, 264, ("prefill_pair", 128)),
+    # row strides past the stage copies' offsets: the LDS-tiled kernel, which the
+    # plan does not see (it is not told the stride)
+    (66, 100, 128, 1, 1 << 27, None), (66, 100, 256, 2, 1 << 27, None),
 ])
-def test_gemm_prefill_pipeline_edges(M, N, K, splits, ldx):
-    """Shortest stage pipelines of every prefill kernel, ragged rows and
-    columns, row strides larger than K up to those that leave the pipelined
-    kernels; NaN between the rows."""
+def test_gemm_prefill_pipeline_edges(M, N, K, splits, ldx, plan):
+    """Shortest stage pipelines of every prefill kernel (the planned kernel is
+    asserted), ragged rows and columns, row strides larger than K up to those
+    that leave the pipelined kernels; NaN between the rows."""
+    if plan:
+        assert lp.op_gemm_plan(M, N, K, splits)[:2] == plan
     rng = np.random.default_rng(M + N + K)
     X, W = bf16_values(rng, (M, K)), bf16_values(rng, (N, K), 0.02)
     if ldx < 1 << 20:
@@ -155,6 +164,9 @@ def test_gemm_prefill_pipeline_edges(M, N, K, splits, ldx):
     ref = X.astype(np.float64) @ W.astype(np.float64).T
     bound = 1e-5 * (np.abs(X.astype(np.float64)) @ np.abs(W.astype(np.float64)).T) + 1e-12
     assert np.all(np.abs(Y[:M].cpu().numpy() - ref) <= bound)
+    if not plan:  # 17 GB of strides
+        del Xd
+        torch.cuda.empty_cache()
 
 
 @pytest.mark.parametrize("half", ["bf16", "f16"])
