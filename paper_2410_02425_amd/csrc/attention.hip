@@ -702,6 +702,9 @@ __device__ __forceinline__ float half_swap_sum(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// Rows of a sequence that are computed: as many as its row of the block table
+// holds.  A tile of 128 rows can reach past max_len, by up to one block.
+__device__ __forceinline__ int prefill_len(int len, const KVCache &kv) { return min(len, kv.max_blocks * KV_BLOCK); }
 template <typename T>
 __device__ __forceinline__ typename Mfma<T>::v8 pack8(const float *p) {
   typedef __typeof__((typename Mfma<T>::v8){}[0]) elem_t;
@@ -776,7 +779,7 @@ __global__ __launch_bounds__(QW *KG * 64, 2) void prefill_attn_mfma_kernel(const
   const int qt = (int)(seq_major ? gridDim.y - 1 - blockIdx.y : gridDim.z - 1 - blockIdx.z);
   const int j = (int)(seq_major ? blockIdx.z : blockIdx.y);
   const int row0 = seq_start[j];
-  const int len = seq_start[j + 1] - row0;
+  const int len = prefill_len(seq_start[j + 1] - row0, kv);
   if (qt * QW * 32 >= len) return;
   const int slot = seq_slot[j];
   const int g = h / (n_heads / kv.n_kv_heads);
@@ -1028,7 +1031,7 @@ __global__ __launch_bounds__(STAGED ? 128 : 64, 3) void prefill_attn_block_kerne
   const int j = blockIdx.y;
   const int qt = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int row0 = seq_start[j];
-  const int len = seq_start[j + 1] - row0;
+  const int len = prefill_len(seq_start[j + 1] - row0, kv);
   if (len <= 0) return;
   const int64_t base = kv_block_base(kv, layer, seq_slot[j], 0, h / (n_heads / kv.n_kv_heads));
   const T *kb = (const T *)kv.k + base, *vb = (const T *)kv.v + base;

@@ -617,6 +617,28 @@ def test_prefill_attention_scores_of_any_size(dtype, lo, hi, heads, n):
     assert n_bad == 0, heads_bad
 
 
+def test_prefill_attention_stays_inside_the_block_table():
+    """A sequence longer than max_len says: its first max_len rows are right, and
+    no row needs, or reads, a block past the table's max_blocks (the table given
+    is the first three columns of a wider one)."""
+    rng = np.random.default_rng(4)
+    Hq, Hkv, hd, n, max_len = 8, 8, 128, 200, 130
+    (kc, vt, bt), Ks, Vs = make_paged_cache(rng, [n], Hkv, hd, torch.float16)
+    q = bf16_values(rng, (n, Hq, hd))
+    out = torch.full((n, Hq, hd), float("nan"), dtype=torch.float16, device=DEV)
+    start = torch.tensor([0, n], dtype=torch.int32, device=DEV)
+    lp.op_prefill_attention(to_dev(q, torch.float16), out, kc, vt, bt[:, :3], start,
+                            torch.zeros(1, dtype=torch.int32, device=DEV), max_len, Hkv)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    args = (q[:max_len].astype(np.float64), Ks[0].astype(np.float64))
+    pos = np.arange(max_len), np.arange(n)
+    ref = T.attention(*args, Vs[0].astype(np.float64), *pos, Hkv)
+    mag = T.attention(*args, np.abs(Vs[0].astype(np.float64)), *pos, Hkv)
+    assert np.all(np.abs(got[:max_len] - ref) <= attention_tol("f16", ref, mag))
+    assert np.isnan(got[192:]).all()
+
+
 def test_zero_row_calls_through_the_binding():
     """Empty device tensors (null data pointers) through the binding: nothing
     is launched and the outputs of other calls are untouched."""
