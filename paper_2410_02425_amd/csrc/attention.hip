@@ -1166,20 +1166,24 @@ static void launch_prefill_hd(const T *q, T *out, const int32_t *seq_start, cons
     // 31.0 against 30.7.  With several prompts the grid's upper bound says
     // little about the live tiles (3 x 400 tokens: 16.5 against 19.2).
     const int64_t wgs = (int64_t)((max_len + 127) / 128) * n_heads;
-    if (max_len <= 32)
-      prefill_attn_block_kernel<T, HD, false><<<dim3(n_heads, n_seq), 64, 0, s>>>(q, out, seq_start, seq_slot, kv,
-                                                                                  layer, n_heads);
-    else if (max_len <= KV_BLOCK)
-      prefill_attn_block_kernel<T, HD, true><<<dim3(n_heads, n_seq), 128, 0, s>>>(q, out, seq_start, seq_slot, kv,
-                                                                                  layer, n_heads);
-    else if (n_seq == 1 && wgs >= 128 && wgs <= 512)
-      launch_prefill_mfma<T, HD, 4, 2>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
-    else
-      launch_prefill_mfma<T, HD, 4, 1>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
-  } else {
-    const dim3 grid((max_len + 63) / 64, n_heads, n_seq);
-    prefill_attn_kernel<T, HD><<<grid, 256, 0, s>>>(q, out, seq_start, seq_slot, kv, layer, n_heads);
+    if ((((uintptr_t)kv.k | (uintptr_t)kv.v) & 15) == 0) {
+      if (max_len <= 32)
+        prefill_attn_block_kernel<T, HD, false><<<dim3(n_heads, n_seq), 64, 0, s>>>(q, out, seq_start, seq_slot, kv,
+                                                                                    layer, n_heads);
+      else if (max_len <= KV_BLOCK)
+        prefill_attn_block_kernel<T, HD, true><<<dim3(n_heads, n_seq), 128, 0, s>>>(q, out, seq_start, seq_slot, kv,
+                                                                                    layer, n_heads);
+      else if (n_seq == 1 && wgs >= 128 && wgs <= 512)
+        launch_prefill_mfma<T, HD, 4, 2>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
+      else
+        launch_prefill_mfma<T, HD, 4, 1>(q, out, seq_start, seq_slot, n_seq, max_len, kv, layer, n_heads, s);
+      return;
+    }
   }
+  // fp32, and 16-bit caches off 16 bytes (the kernels above read and copy whole
+  // 16-byte pieces of them)
+  const dim3 grid((max_len + 63) / 64, n_heads, n_seq);
+  prefill_attn_kernel<T, HD><<<grid, 256, 0, s>>>(q, out, seq_start, seq_slot, kv, layer, n_heads);
 }
 
 template <typename T>

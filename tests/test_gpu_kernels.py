@@ -617,6 +617,36 @@ def test_prefill_attention_scores_of_any_size(dtype, lo, hi, heads, n):
     assert n_bad == 0, heads_bad
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,hd,lens,shift", [
+    ("f16", 8, 2, 128, [150, 64, 7], 1), ("bf16", 4, 4, 64, [33, 5], 4), ("bf16", 4, 1, 128, [20], 2),
+])
+def test_prefill_attention_caches_off_16_bytes(dtype, Hq, Hkv, hd, lens, shift):
+    """K and V caches that start off 16 bytes (2, 4 and 8 bytes), which the
+    kernels that copy them into LDS by 16-byte pieces do not take."""
+    rng = np.random.default_rng(shift)
+    tdt = HALF[dtype]
+    (kc, vt, bt), Ks, Vs = make_paged_cache(rng, lens, Hkv, hd, tdt)
+
+    def shifted(t):
+        buf = torch.full((t.numel() + 16,), float("nan"), dtype=tdt, device=DEV)
+        buf[shift:shift + t.numel()] = t.reshape(-1)
+        return buf[shift:shift + t.numel()].view(t.shape)
+
+    q = bf16_values(rng, (sum(lens), Hq, hd))
+    out = torch.empty(sum(lens), Hq, hd, dtype=tdt, device=DEV)
+    start = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device=DEV)
+    lp.op_prefill_attention(to_dev(q, tdt), out, shifted(kc), shifted(vt), bt, start,
+                            torch.arange(len(lens), dtype=torch.int32, device=DEV), max(lens), Hkv)
+    torch.cuda.synchronize()
+    got, r0 = out.float().cpu().numpy(), 0
+    for j, n in enumerate(lens):
+        args = (q[r0:r0 + n].astype(np.float64), Ks[j].astype(np.float64))
+        ref = T.attention(*args, Vs[j].astype(np.float64), np.arange(n), np.arange(n), Hkv)
+        mag = T.attention(*args, np.abs(Vs[j].astype(np.float64)), np.arange(n), np.arange(n), Hkv)
+        assert np.all(np.abs(got[r0:r0 + n] - ref) <= attention_tol(dtype, ref, mag)), j
+        r0 += n
+
+
 def test_prefill_attention_stays_inside_the_block_table():
     """A sequence longer than max_len says: its first max_len rows are right, and
     no row needs, or reads, a block past the table's max_blocks (the table given
