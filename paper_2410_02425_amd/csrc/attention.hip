@@ -755,7 +755,8 @@ __device__ __forceinline__ void store_o32(T *dst, const floatx16_t &o, float inv
 }
 
 // Base-2 score past which the maximum is taken off before the scale: up to here
-// a rounded mc is within 2^-13, an eighth of the f16 rounding of a weight of 1.
+// a rounded mc is within 2^-13, which moves a weight of 1 by 8.5e-5, less than
+// its rounding to 16 bits (2.4e-4 in f16).
 constexpr float PFA_LARGE = 4096.f;
 
 template <typename T, int HD, int QW, int KG>
