@@ -116,7 +116,9 @@ int lp_op_decode_attention_noalloc(int32_t dtype, const void *q, void *out, cons
  * prompt processing): sequence j owns rows [seq_start[j], seq_start[j+1]) of
  * q/out ([rows x Hq x hd]) at positions 0.., and its keys/values are already
  * in the cache of slot seq_slot[j] (layout as above).  max_len bounds every
- * sequence length. */
+ * sequence length: of a longer one, rows from max_len on may be left out, and
+ * none past the max_blocks * 64 positions of its block table row is computed.
+ * 16-bit caches that are not on 16 bytes take a slower kernel. */
 int lp_op_prefill_attention(int32_t dtype, const void *q, void *out, const void *k_cache, const void *v_cache,
                             const int32_t *block_table, int32_t max_blocks, int64_t n_blocks,
                             const int32_t *seq_start, const int32_t *seq_slot, int32_t n_seq, int32_t max_len,
